@@ -322,6 +322,11 @@ __device__ __forceinline__ float max3f(float a, float b, float c) {
   return r;
 }
 
+// The lowest exp shift m of a thread's sum of e^(z - m): -m log2(e) stays finite, so that logits masked with the
+// type's lowest value add 0 as -inf does (at m = -3.4e38 their terms were inf, and the row's sum NaN).  A row with
+// nothing above it has the sum 0.
+constexpr float kShiftMin = -1e38f;
+
 // Maximum of m and the vector's elements (the exp shift of the row).
 template <typename Tin>
 __device__ __forceinline__ float vec_max(const u32x4& x, float m) {
@@ -367,6 +372,52 @@ __device__ __forceinline__ u32x4 vec_dlogits(const u32x4& x, const RowScale& rs,
     }
   }
   return o;
+}
+
+// ---- rows that start at any element -------------------------------------------
+// A row of V elements at any element-aligned address: `head` elements up to the first 16-byte boundary (fewer than a
+// vector holds), `nvec` whole 16-byte vectors, `tail` elements after them.  The vectors run through the same code as
+// an aligned row's; the at most 14 edge elements (6 in fp32) go to the first threads of the workgroup, one each.
+// RAG = false: the caller knows that every row is whole aligned vectors, and the split is constant.
+// HBM-bound like the aligned rows.  Reading a ragged row element by element, three times, cost four times as much:
+// the loss and dlogits of bf16 6,007 x 151,669 (columns padded to 151,936) took 3.16 ms and take 0.73 (5.0 TB/s),
+// 9,001 x 32,003 took 0.81 and take 0.22 (5.3 TB/s).
+struct RowSplit {
+  int head, nvec, tail;
+};
+template <typename Tin, bool RAG>
+__device__ __forceinline__ RowSplit row_split(const Tin* row, int64_t V) {
+  constexpr int EPV = 16 / (int)sizeof(Tin);
+  if constexpr (!RAG) return RowSplit{0, (int)(V / EPV), 0};
+  const int past = (int)(reinterpret_cast<uintptr_t>(row) & 15) / (int)sizeof(Tin);
+  RowSplit sp;
+  sp.head = (int)min((int64_t)((EPV - past) & (EPV - 1)), V);
+  sp.nvec = (int)((V - sp.head) / EPV);
+  sp.tail = (int)(V - sp.head) - sp.nvec * EPV;
+  return sp;
+}
+// The column of thread tid's edge element, or -1 if it has none.
+template <typename Tin>
+__device__ __forceinline__ int edge_col(const RowSplit& sp, int tid) {
+  if (tid < sp.head) return tid;
+  return tid < sp.head + sp.tail ? tid + sp.nvec * (16 / (int)sizeof(Tin)) : -1;
+}
+// The vector that holds column `col` of the row (-1 if col < 0 or an edge holds it) and the element within it.
+template <typename Tin>
+__device__ __forceinline__ int vec_of(const RowSplit& sp, int col, int& lane) {
+  constexpr int EPV = 16 / (int)sizeof(Tin);
+  const int c = col - sp.head;
+  lane = c & (EPV - 1);
+  return (col >= 0 && c >= 0 && c < sp.nvec * EPV) ? c / EPV : -1;
+}
+__device__ __forceinline__ float load_elem(const float* p) { return *p; }
+__device__ __forceinline__ float load_elem(const uint16_t* p) { return bf16_to_f32(*p); }
+__device__ __forceinline__ void store_elem(float* p, float v) { *p = v; }
+__device__ __forceinline__ void store_elem(uint16_t* p, float v) { *p = (uint16_t)(pack_bf16(v, 0.f) & 0xffffu); }
+
+// One element of dlogits: column col of a row with scale rs whose logit is z; act is the action's column here, or < 0.
+__device__ __forceinline__ float elem_dlogits(float z, const RowScale& rs, int col, int act) {
+  return col == act ? rs.d_a : rs.sign * __builtin_amdgcn_exp2f(fmaf(z, kLog2e, rs.nc));
 }
 
 template <typename Tin>

@@ -64,6 +64,16 @@ inline double n_groups_of(const grpo_segments* seg, const grpo_loss_params* p) {
 
 inline bool aligned(const void* ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 
+// How the vector row kernels can take rows of V elements, `ld` apart, read at `in` and written at `out` (or not
+// written: NULL): whole aligned vectors, split at the 16-byte boundaries with edge elements, or not at all.  The
+// split needs the same distance to the boundary on both sides in every row, which one ld gives.
+enum class RowForm { kWhole, kRagged, kElements };
+inline RowForm row_form(const void* in, const void* out, int64_t V, int64_t ld, size_t esz) {
+  const int64_t epv = (int64_t)(16 / esz);
+  if (V % epv == 0 && ld % epv == 0 && aligned(in, 16) && aligned(out, 16)) return RowForm::kWhole;
+  return (!out || ((uintptr_t)in - (uintptr_t)out) % 16 == 0) ? RowForm::kRagged : RowForm::kElements;
+}
+
 // Compute units of the device the stream belongs to (which need not be the current device), or 0 if the
 // runtime cannot say.
 inline int stream_cu_count(hipStream_t s) {

@@ -47,15 +47,13 @@ __device__ __forceinline__ void fold(float z, float nmb, float& s, float& t) {
   if constexpr (ENT) t = fmaf(e, fmaxf(w, -FLT_MAX), t);
 }
 
-// Raises the shift to mn >= m: s and t are re-expressed relative to mn.
+// Raises the shift m >= kShiftMin to mn: s and t are re-expressed relative to mn.
 template <bool ENT = true>
 __device__ __forceinline__ void rescale(float& m, float mn, float& s, float& t) {
   if (mn > m) {
-    if (m != -INFINITY) {
-      const float dl = (mn - m) * kLog2e, f = __builtin_amdgcn_exp2f(-dl);
-      if constexpr (ENT) t = f * fmaf(-dl, s, t);
-      s *= f;
-    }
+    const float dl = (mn - m) * kLog2e, f = __builtin_amdgcn_exp2f(-dl);
+    if constexpr (ENT) t = f * fmaf(-dl, s, t);
+    s *= f;
     m = mn;
   }
 }
@@ -70,9 +68,9 @@ __device__ __forceinline__ void block_combine3(float m, float s, float t, float*
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const double L = (double)kLog2e;
   const float mw = wave_max_dpp(m);
-  const double f = (m == -INFINITY) ? 0.0 : (double)__builtin_amdgcn_exp2f((m - mw) * kLog2e);
+  const double f = (double)__builtin_amdgcn_exp2f((m - mw) * kLog2e);
   const double sw = wave_sum_dpp(f * (double)s);
-  const double tw = wave_sum_dpp(m == -INFINITY ? 0.0 : f * ((double)t + ((double)m - (double)mw) * L * (double)s));
+  const double tw = wave_sum_dpp(f * ((double)t + ((double)m - (double)mw) * L * (double)s));
   if (lane == 0) {
     sh_m[wv] = mw;
     sh_s[wv] = sw;
@@ -108,7 +106,7 @@ __device__ __forceinline__ void row_out(const LogpArgs& a, int t, double M, doub
                                         bool act_ok) {
   if (a.stats) {
     grpo_vocab_stats r;
-    r.m = M;  // the maximum of stored values: exact
+    r.m = (M == (double)kShiftMin && S == 0.0) ? -INFINITY : M;  // the maximum of stored values: exact
     r.s = S;
     r.z_a = act_ok ? za : -INFINITY;
     a.stats[t] = r;
@@ -125,22 +123,28 @@ __device__ __forceinline__ void row_out(const LogpArgs& a, int t, double M, doub
   }
 }
 
-// Rows of 16-byte vectors (V a multiple of the vector width, 16-byte aligned rows).  ENT: the entropy moment
-// is accumulated (not for a shard's records or a call without an entropy output).
-template <typename Tin, int NT, int U, bool ENT>
+// ENT: the entropy moment is accumulated (not for a shard's records or a call without an entropy output).  RAG: rows
+// that are not whole aligned vectors (RowSplit); an edge element is folded after its thread's vectors.
+template <typename Tin, int NT, int U, bool ENT, bool RAG>
 __global__ __launch_bounds__(NT) void k_logp_vec(const LogpArgs a) {
   constexpr int EPV = 16 / sizeof(Tin), NW = NT / 64;
   __shared__ float sh_m[NW];
   __shared__ double sh_s[NW], sh_t[NW];
   __shared__ float sh_za;
   const int t = blockIdx.x, tid = threadIdx.x;
-  const int nvec = (int)(a.V / EPV);
-  const u32x4* row = reinterpret_cast<const u32x4*>(static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld);
+  const Tin* row0 = static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld;
+  const RowSplit sp = row_split<Tin, RAG>(row0, a.V);
+  const int nvec = sp.nvec;
+  const u32x4* row = reinterpret_cast<const u32x4*>(row0 + sp.head);
   const int64_t act64 = (int64_t)a.actions[t] - a.v_begin;
   const bool act_ok = act64 >= 0 && act64 < a.V;
-  const int act = act_ok ? (int)act64 : 0;
-  const int act_vec = act_ok ? act / EPV : -1;
-  float m = -INFINITY, s = 0.f, tt = 0.f;
+  const int act = act_ok ? (int)act64 : -1;
+  int act_lane;
+  const int act_vec = vec_of<Tin>(sp, act, act_lane);
+  float m = kShiftMin, s = 0.f, tt = 0.f;
+  const int ecol = RAG ? edge_col<Tin>(sp, tid) : -1;
+  float ez = -INFINITY;
+  if (RAG && ecol >= 0) ez = load_elem(row0 + ecol);
   for (int base = tid; base < nvec; base += NT * U) {
     u32x4 x[U];
 #pragma unroll
@@ -154,11 +158,11 @@ __global__ __launch_bounds__(NT) void k_logp_vec(const LogpArgs a) {
       const int vi = base + u * NT;
       if (vi < nvec) {
         cm = vec_max<Tin>(x[u], cm);
-        if (vi == act_vec) sh_za = elem<Tin>(x[u], act % EPV);
+        if (vi == act_vec) sh_za = elem<Tin>(x[u], act_lane);
       }
     }
     rescale<ENT>(m, cm, s, tt);
-    const float nmb = (m == -INFINITY) ? 0.f : -m * kLog2e;
+    const float nmb = -m * kLog2e;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int vi = base + u * NT;
@@ -168,60 +172,31 @@ __global__ __launch_bounds__(NT) void k_logp_vec(const LogpArgs a) {
       }
     }
   }
+  if (RAG && ecol >= 0) {
+    rescale<ENT>(m, fmaxf(m, ez), s, tt);
+    fold<ENT>(ez, -m * kLog2e, s, tt);
+    if (ecol == act) sh_za = ez;
+  }
   double M, S, Tsum;
   block_combine3<NW>(m, s, tt, sh_m, sh_s, sh_t, M, S, Tsum);  // its barrier publishes sh_za
   if (tid == 0) row_out<Tin>(a, t, M, S, Tsum, act_ok ? (double)sh_za : 0.0, act_ok);
 }
 
-template <typename Tin>
-__device__ __forceinline__ float load_one(const Tin* p);
-template <>
-__device__ __forceinline__ float load_one<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float load_one<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
-
-// Any V, ld and element alignment: element loads, the row read twice (shift, then sums).
-template <typename Tin>
-__global__ __launch_bounds__(256) void k_logp_generic(const LogpArgs a) {
-  constexpr int NT = 256, NW = NT / 64;
-  __shared__ float sh_m[NW];
-  __shared__ double sh_s[NW], sh_t[NW];
-  const int t = blockIdx.x, tid = threadIdx.x;
-  const Tin* row = static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld;
-  float m = -INFINITY;
-  for (int64_t v = tid; v < a.V; v += NT) m = fmaxf(m, load_one<Tin>(row + v));
-  const float nmb = (m == -INFINITY) ? 0.f : -m * kLog2e;
-  float s = 0.f, tt = 0.f;
-  if (m != -INFINITY)
-    for (int64_t v = tid; v < a.V; v += NT) fold(load_one<Tin>(row + v), nmb, s, tt);
-  double M, S, Tsum;
-  block_combine3<NW>(m, s, tt, sh_m, sh_s, sh_t, M, S, Tsum);
-  if (tid == 0) {
-    const int64_t act = (int64_t)a.actions[t] - a.v_begin;
-    const bool act_ok = act >= 0 && act < a.V;
-    row_out<Tin>(a, t, M, S, Tsum, act_ok ? (double)load_one<Tin>(row + act) : 0.0, act_ok);
-  }
-}
-
 __global__ void k_clear_flag(int32_t* f) { *f = 0; }
 
-// One workgroup per row: the vector kernel when rows are whole 16-byte vectors, else the element kernel.
+typedef void (*LogpKernel)(const LogpArgs);
+template <typename Tin>
+static LogpKernel logp_kernel(bool ent, bool rag) {
+  if (ent) return rag ? k_logp_vec<Tin, 256, 4, true, true> : k_logp_vec<Tin, 256, 4, true, false>;
+  return rag ? k_logp_vec<Tin, 256, 4, false, true> : k_logp_vec<Tin, 256, 4, false, false>;
+}
+
+// One workgroup per row.
 static void launch_logp(const LogpArgs& a, grpo_dtype dt, hipStream_t s) {
-  const int esz = (dt == GRPO_BF16) ? 2 : 4, epv = 16 / esz;
-  const bool vec = a.V % epv == 0 && a.ld % epv == 0 && aligned(a.logits, 16);
-  const dim3 grid((unsigned)a.T);
+  const bool rag = row_form(a.logits, nullptr, a.V, a.ld, dt == GRPO_BF16 ? 2 : 4) == RowForm::kRagged;
   const bool ent = a.entropy && !a.stats;
-  if (vec && dt == GRPO_BF16) {
-    if (ent) hipLaunchKernelGGL((k_logp_vec<uint16_t, 256, 4, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_logp_vec<uint16_t, 256, 4, false>), grid, dim3(256), 0, s, a);
-  } else if (vec) {
-    if (ent) hipLaunchKernelGGL((k_logp_vec<float, 256, 4, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_logp_vec<float, 256, 4, false>), grid, dim3(256), 0, s, a);
-  } else if (dt == GRPO_BF16) {
-    hipLaunchKernelGGL(k_logp_generic<uint16_t>, grid, dim3(256), 0, s, a);
-  } else {
-    hipLaunchKernelGGL(k_logp_generic<float>, grid, dim3(256), 0, s, a);
-  }
+  const LogpKernel k = dt == GRPO_BF16 ? logp_kernel<uint16_t>(ent, rag) : logp_kernel<float>(ent, rag);
+  hipLaunchKernelGGL(k, dim3((unsigned)a.T), dim3(256), 0, s, a);
 }
 
 hipError_t launch_vocab_records(const void* logits, grpo_dtype dt, int64_t T, int64_t V, int64_t ld,

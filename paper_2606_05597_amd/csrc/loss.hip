@@ -11,12 +11,16 @@
 //                   while row t's dlogits are written: part of each row lives
 //                   in LDS (global_load_lds), the rest in registers.
 //  k_rows_resident  shorter rows: one workgroup per row, several per CU.
-//  two passes       vector rows too long for either (fp32 beyond 77,824
+//  Rows that are not whole 16-byte vectors (odd vocabularies, strides or
+//  addresses) take the same kernels, split at the 16-byte boundaries into
+//  vectors and at most 14 edge elements (device.h RowSplit).
+//  two passes       rows too long for either (fp32 beyond 77,824
 //                   columns, bf16 beyond 188,416): each row reduced to a
 //                   record (logp.hip), then the record turned into the token
 //                   epilogue and the row's dlogits (vocab.hip); the row is
 //                   read twice.
-//  k_rows_generic   any V, stride or alignment: element loads, three sweeps.
+//  k_rows_generic   dlogits at another distance from a 16-byte boundary than the
+//                   logits: element loads, three sweeps.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -41,13 +45,6 @@ struct RowArgs {
   int chunk2;     // k_rows_pipe: rows [r0, T) go chunk2 at a time, one chunk per workgroup (>= 1)
   TokenArgs tok;
 };
-
-template <typename Tin>
-__device__ __forceinline__ float load_elem(const Tin* p);
-template <>
-__device__ __forceinline__ float load_elem<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float load_elem<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
 
 // Element e of a 16-byte vector (8 bf16 or 4 fp32), widened to fp32.
 template <typename Tin>
@@ -225,13 +222,18 @@ __device__ __forceinline__ void fresh(u32x4 (&v)[N]) {
 }
 
 // Each thread owns NV vectors of 8 bf16, with (NV-1)*1024 < V/8 <= NV*1024 so
-// that only the last vector can be partial.  The first NP live in LDS (staged
+// that only the last vector can be partial.  RAG: rows that are not whole aligned
+// vectors (RowSplit).  A row then has floor(V/8) or floor(V/8) - 1 vectors, so all
+// but the last are still whole; a thread's edge element travels in a register, loaded
+// before the next row's LDS part is staged, so that the waits count the same
+// operations; and the LDS part keeps its logits, not their fp16 terms, so that
+// dlogits are formed in fp32 throughout (the terms are worth 0.3%).  The first NP live in LDS (staged
 // with buffer loads straight to LDS and read back in every pass), the other
 // NR = NV - NP in registers.  Once the row's lse is known, dlogits are written
 // first for the LDS part, which is then re-staged with the next row, and then
 // for the register part, whose registers are then reloaded with the next
 // row's vectors.
-template <int NV, int NP>
+template <int NV, int NP, bool RAG>
 __global__ __launch_bounds__(1024) void k_rows_pipe(const RowArgs a) {
   constexpr int NT = 1024, NW = NT / 64, NR = NV - NP, VB = NT * 16;  // VB: bytes per vector slot
   __shared__ __attribute__((aligned(16))) u32x4 stage[NP * NT];
@@ -240,20 +242,21 @@ __global__ __launch_bounds__(1024) void k_rows_pipe(const RowArgs a) {
   __shared__ float sh_za;
   __shared__ TokenIn sh_in;  // inputs of the row about to start (wave 1 loads them during the previous row)
   const int wv = threadIdx.x >> 6;
-  const int nvec = (int)(a.tok.V / 8);
-  const int row_bytes = nvec * 16;
   const uint16_t* logits = static_cast<const uint16_t*>(a.logits);
   uint16_t* dlogits = static_cast<uint16_t*>(a.dlogits);
+  auto split = [&](int r) { return row_split<uint16_t, RAG>(logits + (int64_t)r * a.ld, a.tok.V); };
 
   const uint32_t lds_stage =
       (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) u32x4*)stage) + wv * 64 * 16;
   auto stage_row = [&](int r, int voff) {  // vectors 0..NP-1 of row r -> LDS, asynchronously
-    const u32x4 src = row_rsrc_words(logits + (int64_t)r * a.ld, (uint32_t)row_bytes);
+    const RowSplit sp = split(r);
+    const u32x4 src = row_rsrc_words(logits + (int64_t)r * a.ld + sp.head, (uint32_t)sp.nvec * 16u);
 #pragma unroll
     for (int j = 0; j < NP; ++j) dma16_nt(lds_stage + j * NT * 16, voff, j * VB, src);
   };
   auto load_regs = [&](u32x4 (&dst)[NR], int r, int voff) {
-    const __amdgpu_buffer_rsrc_t src = row_rsrc(logits + (int64_t)r * a.ld, row_bytes);
+    const RowSplit sp = split(r);
+    const __amdgpu_buffer_rsrc_t src = row_rsrc(logits + (int64_t)r * a.ld + sp.head, sp.nvec * 16);
 #pragma unroll
     for (int q = 0; q < NR; ++q) dst[q] = __builtin_amdgcn_raw_buffer_load_b128(src, voff, (NP + q) * VB, kStream);
   };
@@ -275,6 +278,12 @@ __global__ __launch_bounds__(1024) void k_rows_pipe(const RowArgs a) {
   int t = R0 > 0 ? (int)blockIdx.x * C : R0 + (int)blockIdx.x * C2;
   if (t >= a.T) return;
   u32x4 reg[NR];
+  float ez = -INFINITY;  // RAG: the thread's edge element of row t
+  auto load_edge = [&](int r, int tid) {
+    const int c = edge_col<uint16_t>(split(r), tid);
+    return c >= 0 ? load_elem(logits + (int64_t)r * a.ld + c) : -INFINITY;
+  };
+  if constexpr (RAG) ez = load_edge(t, threadIdx.x);
   if (threadIdx.x == 64) sh_in = token_load(a.tok, t);
   stage_row(t, threadIdx.x * 16);
   load_regs(reg, t, threadIdx.x * 16);
@@ -286,29 +295,36 @@ __global__ __launch_bounds__(1024) void k_rows_pipe(const RowArgs a) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int voff = tid * 16;
-    const bool last_full = tid < nvec - (NV - 1) * NT;
+    const RowSplit sp = split(t);
+    const bool last_full = tid < sp.nvec - (NV - 1) * NT;
     const int tn = next_row(t);
     t_next = tn;
     lds_barrier();  // every wave's LDS part of row t has landed, and sh_in holds row t's inputs
     const TokenIn in = sh_in;
-    const int act_vec = (in.act >= 0 && in.act < a.tok.V) ? in.act / 8 : -1;
-    const int act_lane = in.act & 7;
+    const bool act_ok = in.act >= 0 && in.act < a.tok.V;
+    int act_lane;
+    const int act_vec = vec_of<uint16_t>(sp, act_ok ? in.act : -1, act_lane);
+    const int ecol = RAG ? edge_col<uint16_t>(sp, tid) : -1;
 
     // (max, sum exp) over the LDS part first, while the register part is still landing
-    float m1 = -INFINITY;
+    float m1 = kShiftMin;
 #pragma unroll 1
     for (int j = 0; j < NP; ++j) {
       const u32x4 x = stage[j * NT + tid];
       m1 = vec_max<uint16_t>(x, m1);
       if (j * NT + tid == act_vec) sh_za = vec_elem<uint16_t>(x, act_lane);
     }
-    const float nmb1 = (m1 == -INFINITY) ? 0.f : -m1 * kLog2e;
+    const float nmb1 = -m1 * kLog2e;
     float s1 = 0.f;
 #pragma unroll 1
     for (int j = 0; j < NP; ++j) {  // the terms replace the logits in the thread's own LDS slots
       u32x4 x = stage[j * NT + tid];
-      s1 += vec_sumexp_keep(x, nmb1);
-      stage[j * NT + tid] = x;
+      if constexpr (RAG) {
+        s1 += vec_sumexp<uint16_t>(x, nmb1);
+      } else {
+        s1 += vec_sumexp_keep(x, nmb1);
+        stage[j * NT + tid] = x;
+      }
     }
     float m = m1;
 #pragma unroll
@@ -319,8 +335,13 @@ __global__ __launch_bounds__(1024) void k_rows_pipe(const RowArgs a) {
         if (j * NT + tid == act_vec) sh_za = vec_elem<uint16_t>(reg[q], act_lane);
       }
     }
-    const float nmb = (m == -INFINITY) ? 0.f : -m * kLog2e;
-    float s = (m1 == -INFINITY) ? 0.f : s1 * __builtin_amdgcn_exp2f((m1 - m) * kLog2e);
+    if constexpr (RAG) {
+      m = fmaxf(m, ez);
+      if (act_ok && ecol == in.act) sh_za = ez;
+    }
+    const float nmb = -m * kLog2e;
+    float s = s1 * __builtin_amdgcn_exp2f((m1 - m) * kLog2e);
+    if constexpr (RAG) s += __builtin_amdgcn_exp2f(fmaf(ez, kLog2e, nmb));  // no edge: exp2(-inf) = 0
     fresh(reg);
 #pragma unroll
     for (int q = 0; q < NR; ++q)
@@ -339,20 +360,29 @@ __global__ __launch_bounds__(1024) void k_rows_pipe(const RowArgs a) {
 
     const uint32_t smask = sign_mask<uint16_t>(rs);
     const float c1 = rs.sign * __builtin_amdgcn_exp2f(rs.nc - nmb1);  // the LDS part's terms: d = c1 e
-    const int act_v = rs.act >= 0 ? rs.act / 8 : -1;
+    int act_l;
+    const int act_v = vec_of<uint16_t>(sp, rs.act, act_l);
     fresh(reg);
     // forward only: a zero-sized destination, so the range check drops every store
     const bool write = dlogits != nullptr;
-    const __amdgpu_buffer_rsrc_t dst = row_rsrc(write ? dlogits + (int64_t)t * a.ld : logits, write ? row_bytes : 0);
+    const __amdgpu_buffer_rsrc_t dst = row_rsrc(write ? dlogits + (int64_t)t * a.ld + sp.head : logits, write ? sp.nvec * 16 : 0);
 #pragma unroll 1
-    for (int j = 0; j < NP; ++j)
-      __builtin_amdgcn_raw_buffer_store_b128(
-          vec_dlogits_kept(stage[j * NT + tid], c1, j * NT + tid == act_v, rs.act & 7, rs.d_a), dst, voff, j * VB,
-          kStream);
+    for (int j = 0; j < NP; ++j) {
+      u32x4 d;
+      if constexpr (RAG) d = vec_dlogits<uint16_t>(stage[j * NT + tid], rs, smask, j * NT + tid == act_v, act_l);
+      else d = vec_dlogits_kept(stage[j * NT + tid], c1, j * NT + tid == act_v, act_l, rs.d_a);
+      __builtin_amdgcn_raw_buffer_store_b128(d, dst, voff, j * VB, kStream);
+    }
+    if constexpr (RAG) {
+      if (write && ecol >= 0) store_elem(dlogits + (int64_t)t * a.ld + ecol, elem_dlogits(ez, rs, ecol, rs.act));
+      ez = load_edge(tn < a.T ? tn : t, tid);
+    }
     lds_barrier();  // every wave is done reading stage[] (the stores read registers)
     if (tn < a.T) stage_row(tn, voff);
     // past the last row: a zero-sized source, every load returns 0
-    const __amdgpu_buffer_rsrc_t nxt = row_rsrc(logits + (int64_t)(tn < a.T ? tn : t) * a.ld, tn < a.T ? row_bytes : 0);
+    const RowSplit spn = split(tn < a.T ? tn : t);
+    const __amdgpu_buffer_rsrc_t nxt =
+        row_rsrc(logits + (int64_t)(tn < a.T ? tn : t) * a.ld + spn.head, tn < a.T ? spn.nvec * 16 : 0);
     // All of the register part's stores, then all of its loads: a burst in each direction per wave runs 7-8%
     // faster than alternating store and load per vector.  Each store is followed by two wait states: the compiler
     // reuses a store's data registers in the very next instruction (it inserts no wait for a 16-byte buffer store
@@ -361,7 +391,7 @@ __global__ __launch_bounds__(1024) void k_rows_pipe(const RowArgs a) {
     for (int q = 0; q < NR; ++q) {
       const int j = NP + q;
       __builtin_amdgcn_raw_buffer_store_b128(
-          vec_dlogits<uint16_t>(reg[q], rs, smask, j * NT + tid == act_v, rs.act & 7), dst, voff, j * VB, kStream);
+          vec_dlogits<uint16_t>(reg[q], rs, smask, j * NT + tid == act_v, act_l), dst, voff, j * VB, kStream);
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("s_nop 1" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
@@ -375,11 +405,10 @@ __global__ __launch_bounds__(1024) void k_rows_pipe(const RowArgs a) {
 }
 
 // ---- register-resident row kernel -------------------------------------------
-// NT threads per row, NV 16-byte vectors per thread: V <= NT*NV*EPV.  Rows are
-// 16-byte aligned and V is a multiple of EPV (checked on the host).
-template <typename Tin, int NT, int NV>
+// NT threads per row, NV 16-byte vectors per thread: V/EPV <= NT*NV.  RAG: rows that
+// are not whole aligned vectors (RowSplit), otherwise they are (checked on the host).
+template <typename Tin, int NT, int NV, bool RAG>
 __global__ __launch_bounds__(NT) void k_rows_resident(const RowArgs a) {
-  constexpr int EPV = 16 / sizeof(Tin);  // elements per vector: 8 bf16 or 4 fp32
   constexpr int NW = NT / 64;
   __shared__ float sh_m[NW];
   __shared__ double sh_s[NW];
@@ -387,11 +416,17 @@ __global__ __launch_bounds__(NT) void k_rows_resident(const RowArgs a) {
 
   const int t = blockIdx.x;
   const int tid = threadIdx.x;
-  const int nvec = (int)(a.tok.V / EPV);
-  const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld);
+  const Tin* row = static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld;
+  const RowSplit sp = row_split<Tin, RAG>(row, a.tok.V);
+  const int nvec = sp.nvec;
+  const u32x4* src = reinterpret_cast<const u32x4*>(row + sp.head);
   const TokenIn in = token_load(a.tok, t);
-  const int act_vec = (in.act >= 0 && in.act < a.tok.V) ? in.act / EPV : -1;
-  const int act_lane = in.act % EPV;
+  const bool act_ok = in.act >= 0 && in.act < a.tok.V;
+  int act_lane;
+  const int act_vec = vec_of<Tin>(sp, act_ok ? in.act : -1, act_lane);
+  const int ecol = RAG ? edge_col<Tin>(sp, tid) : -1;
+  float ez = -INFINITY;
+  if (RAG && ecol >= 0) ez = load_elem(row + ecol);
 
   u32x4 buf[NV];
 #pragma unroll
@@ -399,7 +434,7 @@ __global__ __launch_bounds__(NT) void k_rows_resident(const RowArgs a) {
     const int vi = j * NT + tid;
     if (vi < nvec) buf[j] = __builtin_nontemporal_load(src + vi);
   }
-  float m = -INFINITY;
+  float m = kShiftMin;
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int vi = j * NT + tid;
@@ -408,8 +443,12 @@ __global__ __launch_bounds__(NT) void k_rows_resident(const RowArgs a) {
       if (vi == act_vec) sh_za = vec_elem<Tin>(buf[j], act_lane);
     }
   }
-  const float nmb = (m == -INFINITY) ? 0.f : -m * kLog2e;
-  float s = 0.f;
+  if constexpr (RAG) {
+    m = fmaxf(m, ez);
+    if (act_ok && ecol == in.act) sh_za = ez;
+  }
+  const float nmb = -m * kLog2e;
+  float s = RAG ? __builtin_amdgcn_exp2f(fmaf(ez, kLog2e, nmb)) : 0.f;  // no edge: exp2(-inf) = 0
 #pragma unroll
   for (int j = 0; j < NV; ++j)
     if (j * NT + tid < nvec) s += vec_sumexp<Tin>(buf[j], nmb);
@@ -423,20 +462,23 @@ __global__ __launch_bounds__(NT) void k_rows_resident(const RowArgs a) {
   if (!a.dlogits) return;
 
   const uint32_t smask = sign_mask<Tin>(rs);
-  u32x4* dst = reinterpret_cast<u32x4*>(static_cast<Tin*>(a.dlogits) + (int64_t)t * a.ld);
+  Tin* drow = static_cast<Tin*>(a.dlogits) + (int64_t)t * a.ld;
+  u32x4* dst = reinterpret_cast<u32x4*>(drow + sp.head);
+  int act_l;
+  const int act_v = vec_of<Tin>(sp, rs.act, act_l);
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int vi = j * NT + tid;
     if (vi < nvec)
-      __builtin_nontemporal_store(vec_dlogits<Tin>(buf[j], rs, smask, vi == rs.act / EPV && rs.act >= 0,
-                                                   rs.act % EPV),
-                                  dst + vi);
+      __builtin_nontemporal_store(vec_dlogits<Tin>(buf[j], rs, smask, vi == act_v, act_l), dst + vi);
   }
+  if (RAG && ecol >= 0) store_elem(drow + ecol, elem_dlogits(ez, rs, ecol, rs.act));
 }
 
 // ---- generic row kernel ------------------------------------------------------
 // Any V, ld and element alignment: element-wise loads, the row read three
-// times (max, sum, dlogits).  Used when the vector kernels do not apply.
+// times (max, sum, dlogits).  Used when the vector kernels do not apply: dlogits
+// at another distance from a 16-byte boundary than the logits.
 template <typename Tin>
 __global__ __launch_bounds__(256) void k_rows_generic(const RowArgs a) {
   constexpr int NT = 256, NW = NT / 64;
@@ -447,29 +489,22 @@ __global__ __launch_bounds__(256) void k_rows_generic(const RowArgs a) {
   const Tin* row = static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld;
   const TokenIn in = token_load(a.tok, t);
   float m = -INFINITY;
-  for (int64_t v = tid; v < a.tok.V; v += NT) m = fmaxf(m, load_elem<Tin>(row + v));
+  for (int64_t v = tid; v < a.tok.V; v += NT) m = fmaxf(m, load_elem(row + v));
   const float nmb = (m == -INFINITY) ? 0.f : -m * kLog2e;
   float s = 0.f;
-  for (int64_t v = tid; v < a.tok.V; v += NT) s += __builtin_amdgcn_exp2f(fmaf(load_elem<Tin>(row + v), kLog2e, nmb));
+  for (int64_t v = tid; v < a.tok.V; v += NT) s += __builtin_amdgcn_exp2f(fmaf(load_elem(row + v), kLog2e, nmb));
   double M, S;
   block_combine<NW>(m, s, sh_m, sh_s, M, S);
   if (tid == 0) {
     const bool ok = in.act >= 0 && (int64_t)in.act < a.tok.V;
-    sh_rs = token_finish(a.tok, t, in, row_lse(M, S), ok ? (double)load_elem<Tin>(row + in.act) : 0.0);
+    sh_rs = token_finish(a.tok, t, in, row_lse(M, S), ok ? (double)load_elem(row + in.act) : 0.0);
   }
   __syncthreads();
   if (!a.dlogits) return;
   const RowScale rs = sh_rs;
   Tin* drow = static_cast<Tin*>(a.dlogits) + (int64_t)t * a.ld;
-  for (int64_t v = tid; v < a.tok.V; v += NT) {
-    const float d =
-        (v == rs.act) ? rs.d_a : rs.sign * __builtin_amdgcn_exp2f(fmaf(load_elem<Tin>(row + v), kLog2e, rs.nc));
-    if constexpr (sizeof(Tin) == 2) {
-      drow[v] = (uint16_t)(pack_bf16(d, 0.f) & 0xffffu);
-    } else {
-      drow[v] = d;
-    }
-  }
+  for (int64_t v = tid; v < a.tok.V; v += NT)
+    store_elem(drow + v, elem_dlogits(load_elem(row + v), rs, (int)v, rs.act));
 }
 
 // ---- dispatch ------------------------------------------------------------------
@@ -477,11 +512,14 @@ typedef void (*RowKernel)(const RowArgs);
 
 struct Variant {
   int nt, nv;
-  RowKernel bf16, f32;
+  RowKernel bf16[2], f32[2];  // whole aligned vectors, ragged
 };
 
-#define GRPO_VARIANT(NT, NV) \
-  { NT, NV, k_rows_resident<uint16_t, NT, NV>, k_rows_resident<float, NT, NV> }
+#define GRPO_VARIANT(NT, NV)                                                                       \
+  {                                                                                                \
+    NT, NV, {k_rows_resident<uint16_t, NT, NV, false>, k_rows_resident<uint16_t, NT, NV, true>},   \
+        {k_rows_resident<float, NT, NV, false>, k_rows_resident<float, NT, NV, true>}              \
+  }
 
 // Searched in order; the first that holds the row is used.  Rows of 3,073 to 4,096 vectors (a bf16 vocabulary of
 // 32,000 among them) take 1024 threads x 4 vectors: 6% faster there than 256 x 16 (0.707 against 0.752 ms at
@@ -495,11 +533,11 @@ static const Variant kVariants[] = {
 
 // The persistent kernels for long bf16 rows, one per NV = ceil(V/8/1024) so
 // that only each thread's last vector can be partial; NP vectors in LDS.
-static const RowKernel kPipe[] = {
-    k_rows_pipe<7, 4>,   k_rows_pipe<8, 4>,   k_rows_pipe<9, 5>,   k_rows_pipe<10, 5>, k_rows_pipe<11, 6>,
-    k_rows_pipe<12, 6>,  k_rows_pipe<13, 7>,  k_rows_pipe<14, 7>,  k_rows_pipe<15, 1>, k_rows_pipe<16, 2>,
-    k_rows_pipe<17, 3>,  k_rows_pipe<18, 4>,  k_rows_pipe<19, 6>,  k_rows_pipe<20, 9>, k_rows_pipe<21, 9>,
-    k_rows_pipe<22, 9>,  k_rows_pipe<23, 9>,
+#define GRPO_PIPE(NV, NP) {k_rows_pipe<NV, NP, false>, k_rows_pipe<NV, NP, true>}
+static const RowKernel kPipe[][2] = {
+    GRPO_PIPE(7, 4),  GRPO_PIPE(8, 4),  GRPO_PIPE(9, 5),  GRPO_PIPE(10, 5), GRPO_PIPE(11, 6), GRPO_PIPE(12, 6),
+    GRPO_PIPE(13, 7), GRPO_PIPE(14, 7), GRPO_PIPE(15, 1), GRPO_PIPE(16, 2), GRPO_PIPE(17, 3), GRPO_PIPE(18, 4),
+    GRPO_PIPE(19, 6), GRPO_PIPE(20, 9), GRPO_PIPE(21, 9), GRPO_PIPE(22, 9), GRPO_PIPE(23, 9),
 };  // from 15 vectors on, 14 in registers and the rest in LDS, except 19 (V = 151,936): 13 and 6, 0.3% faster
    // than 15 and 4 and 0.4% faster than 14 and 5, with 12 and 7 or 11 and 8 within 0.1% of it (before the LDS
    // part kept its terms, 15 and 4 was 0.4% faster than 14 and 5)
@@ -516,9 +554,10 @@ struct Launch {
 static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, const void* logits,
                               const void* dlogits, hipStream_t s) {
   const int epv = (dt == GRPO_BF16) ? 8 : 4;
-  const bool vec_ok = (V % epv == 0) && (ld % epv == 0) && aligned(logits, 16) && aligned(dlogits, 16);
-  if (vec_ok) {
-    const int64_t nvec = V / epv;
+  const RowForm form = row_form(logits, dlogits, V, ld, 16 / epv);
+  const int rag = form == RowForm::kRagged;
+  if (form != RowForm::kElements) {
+    const int64_t nvec = V / epv;  // the most a row has
     const int64_t nv = (nvec + 1023) / 1024;
     if (dt == GRPO_BF16 && nv >= kPipeMinNV && nv <= kPipeMaxNV && T <= kPipeMaxT) {
       int n_cu = stream_cu_count(s);  // of the stream's device
@@ -532,10 +571,10 @@ static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, c
       // 469 rows instead of 472
       const int64_t r0 = T / (chunk * g) * (chunk * g);
       const int64_t chunk2 = std::max<int64_t>(1, (T - r0 + g - 1) / g);
-      return Launch{kPipe[nv - kPipeMinNV], 1024, (unsigned)g, (int)chunk, (int)r0, (int)chunk2};
+      return Launch{kPipe[nv - kPipeMinNV][rag], 1024, (unsigned)g, (int)chunk, (int)r0, (int)chunk2};
     }
     for (const Variant& v : kVariants) {
-      if ((int64_t)v.nt * v.nv >= nvec) return Launch{dt == GRPO_BF16 ? v.bf16 : v.f32, v.nt, (unsigned)T};
+      if ((int64_t)v.nt * v.nv >= nvec) return Launch{dt == GRPO_BF16 ? v.bf16[rag] : v.f32[rag], v.nt, (unsigned)T};
     }
     return Launch{nullptr, 0, 0};  // two passes
   }

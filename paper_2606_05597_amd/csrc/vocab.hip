@@ -50,10 +50,10 @@ __device__ inline void shard_row_head(const ShardArgs& a, int t, RowScale& rs, i
 // Rows of 16-byte vectors, one workgroup per row; U vectors per thread in flight.
 // The row's first U vectors per thread are loaded before the records are merged (the loads do not depend on
 // them), and every wave merges the records and forms the scale itself while they land: no barrier, no one-thread
-// section ahead of the loads.  Thread 0 alone writes the token's outputs.
-template <typename Tin, int NT, int U>
+// section ahead of the loads.  Thread 0 alone writes the token's outputs.  RAG: rows that are not whole aligned
+// vectors (RowSplit).
+template <typename Tin, int NT, int U, bool RAG>
 __global__ __launch_bounds__(NT) void k_shard_rows_vec(const ShardArgs a) {
-  constexpr int EPV = 16 / sizeof(Tin);
   const int t = blockIdx.x, tid = threadIdx.x;
   if (!a.dlogits) {  // forward only: the token's outputs, no row traffic
     if (tid == 0) {
@@ -63,9 +63,15 @@ __global__ __launch_bounds__(NT) void k_shard_rows_vec(const ShardArgs a) {
     }
     return;
   }
-  const int nvec = (int)(a.V / EPV);
-  const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld);
-  u32x4* dst = reinterpret_cast<u32x4*>(static_cast<Tin*>(a.dlogits) + (int64_t)t * a.ld);
+  const Tin* row = static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld;
+  Tin* drow = static_cast<Tin*>(a.dlogits) + (int64_t)t * a.ld;
+  const RowSplit sp = row_split<Tin, RAG>(row, a.V);
+  const int nvec = sp.nvec;
+  const u32x4* src = reinterpret_cast<const u32x4*>(row + sp.head);
+  u32x4* dst = reinterpret_cast<u32x4*>(drow + sp.head);
+  const int ecol = RAG ? edge_col<Tin>(sp, tid) : -1;
+  float ez = 0.f;
+  if (RAG && ecol >= 0) ez = load_elem(row + ecol);
   u32x4 x[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -80,8 +86,10 @@ __global__ __launch_bounds__(NT) void k_shard_rows_vec(const ShardArgs a) {
   if (tid == 0) token_store(a.tok, t, in, ev);
   const int64_t al = rs.act >= 0 ? (int64_t)rs.act - a.v_begin : -1;
   const int act = (al >= 0 && al < a.V) ? (int)al : -1;  // the action's column in this shard, if it holds it
-  const int act_vec = act >= 0 ? act / EPV : -1, act_lane = act >= 0 ? act % EPV : 0;
+  int act_lane;
+  const int act_vec = vec_of<Tin>(sp, act, act_lane);
   const uint32_t smask = sign_mask<Tin>(rs);
+  if (RAG && ecol >= 0) store_elem(drow + ecol, elem_dlogits(ez, rs, ecol, act));
   for (int base = tid; base < nvec; base += NT * U) {
     if (base != tid) {
 #pragma unroll
@@ -98,16 +106,7 @@ __global__ __launch_bounds__(NT) void k_shard_rows_vec(const ShardArgs a) {
   }
 }
 
-template <typename Tin>
-__device__ __forceinline__ float shard_load(const Tin* p);
-template <>
-__device__ __forceinline__ float shard_load<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float shard_load<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
-__device__ __forceinline__ void shard_store(float* p, float v) { *p = v; }
-__device__ __forceinline__ void shard_store(uint16_t* p, float v) { *p = (uint16_t)(pack_bf16(v, 0.f) & 0xffffu); }
-
-// Any V, stride or alignment: element loads and stores.
+// Rows read and written at different distances from a 16-byte boundary: element loads and stores.
 template <typename Tin>
 __global__ __launch_bounds__(256) void k_shard_rows_generic(const ShardArgs a) {
   __shared__ RowScale sh_rs;
@@ -127,8 +126,7 @@ __global__ __launch_bounds__(256) void k_shard_rows_generic(const ShardArgs a) {
   const Tin* src = static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld;
   Tin* dst = static_cast<Tin*>(a.dlogits) + (int64_t)t * a.ld;
   for (int64_t v = tid; v < a.V; v += 256) {
-    const float d = (v == act) ? rs.d_a : rs.sign * __builtin_amdgcn_exp2f(fmaf(shard_load<Tin>(src + v), kLog2e, rs.nc));
-    shard_store(dst + v, d);
+    store_elem(dst + v, elem_dlogits(load_elem(src + v), rs, (int)v, act));
   }
 }
 
@@ -146,13 +144,21 @@ hipError_t launch_shard_rows(const void* logits, void* dlogits, grpo_dtype dt, i
   a.n_shards = n_shards;
   a.stats = stats;
   a.tok = tok;
-  const int epv = (dt == GRPO_BF16) ? 8 : 4;
-  const bool vec = V % epv == 0 && ld % epv == 0 && aligned(logits, 16) && aligned(dlogits, 16);
   const dim3 grid((unsigned)T);
-  if (vec && dt == GRPO_BF16) hipLaunchKernelGGL((k_shard_rows_vec<uint16_t, 512, 5>), grid, dim3(512), 0, s, a);
-  else if (vec) hipLaunchKernelGGL((k_shard_rows_vec<float, 512, 5>), grid, dim3(512), 0, s, a);
-  else if (dt == GRPO_BF16) hipLaunchKernelGGL(k_shard_rows_generic<uint16_t>, grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(k_shard_rows_generic<float>, grid, dim3(256), 0, s, a);
+  const bool bf = dt == GRPO_BF16;
+  switch (row_form(logits, dlogits, V, ld, bf ? 2 : 4)) {
+    case RowForm::kWhole:
+      if (bf) hipLaunchKernelGGL((k_shard_rows_vec<uint16_t, 512, 5, false>), grid, dim3(512), 0, s, a);
+      else hipLaunchKernelGGL((k_shard_rows_vec<float, 512, 5, false>), grid, dim3(512), 0, s, a);
+      break;
+    case RowForm::kRagged:
+      if (bf) hipLaunchKernelGGL((k_shard_rows_vec<uint16_t, 512, 5, true>), grid, dim3(512), 0, s, a);
+      else hipLaunchKernelGGL((k_shard_rows_vec<float, 512, 5, true>), grid, dim3(512), 0, s, a);
+      break;
+    default:
+      if (bf) hipLaunchKernelGGL(k_shard_rows_generic<uint16_t>, grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL(k_shard_rows_generic<float>, grid, dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 

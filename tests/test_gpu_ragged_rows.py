@@ -1,0 +1,135 @@
+"""GPU parity of the row kernels on rows that are not whole 16-byte vectors: odd vocabularies, strides and base
+addresses, at the sizes where the split into edge elements and vectors changes kernel or leaves one of them empty.
+
+The gates are those of tests/gpu_parity.py; bf16 dlogits are held to one rounding of an fp32 value,
+2^-8 |ref| + 1e-5 max_row |ref|, whatever the row length (these rows form dlogits in fp32 throughout).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2606_05597_amd as grpo
+from synth.rollouts import Config, make_structure
+from tests.gpu_parity import LOGP_ATOL, LOSS_RTOL, dl_to_f64, gpu_norm, to_np_logits
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(V, ld, dtype, offset, T=40, seed=3):
+    """T rows of V logits, ld apart, the first `offset` elements past an aligned address; actions in the first and
+    last columns, next to the first boundary, and anywhere."""
+    cfg = Config("ragged", 1, 4, V, "f32", 2.0, 0.5, (2, 3), (2, 3), 4.0, (1, 64), 0.1, 4.0, seed=seed)
+    st = make_structure(cfg, seed, T)
+    g = torch.Generator("cuda").manual_seed(seed)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    store = torch.zeros(T * ld + 32, dtype=dt, device="cuda")
+    lg = store[offset:offset + T * ld].view(T, ld)
+    lg[:, :V] = (2.0 * torch.randn((T, V), generator=g, device="cuda")).to(dt)
+    act = torch.randint(0, V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    for i, a in enumerate([0, V - 1, 1, V - 2, 7, 8, V - 8, V - 9]):
+        act[i] = min(max(a, 0), V - 1)
+    z = lg[:, :V].float()
+    lp = z.gather(1, act.long()[:, None])[:, 0] - torch.logsumexp(z, 1)
+    behave = lp + 0.05 * torch.randn(T, generator=g, device="cuda")
+    adv = oracle.advantages(st.rewards, cfg.G).astype(np.float32)
+    return cfg, st, lg, act, behave, adv
+
+
+def _loss(cfg, st, lg, act, behave, adv, V, dl, gs):
+    aux = grpo.LossAux.alloc(len(act), len(st.rewards), "cuda", which=("token_logp", "error_flags"))
+    loss, _ = grpo.grpo_loss_fwd_bwd(lg, act, behave, torch.from_numpy(adv).cuda(),
+                                     torch.from_numpy(st.step_tok_off).cuda(),
+                                     torch.from_numpy(st.traj_step_off).cuda(), cfg.G, V=V,
+                                     norm=gpu_norm(oracle.NORM_CONST_K), k=cfg.k, dual_clip_c=3.0, grad_scale=gs,
+                                     dlogits=dl, aux=aux)
+    torch.cuda.synchronize()
+    return loss.item(), aux
+
+
+# bf16: below a vector, the resident variants' ends (64 x 1 and 256 x 4 vectors and one more), the persistent kernel's
+# first and last sizes and one between two of its vector counts, a padded head, past it (two passes); fp32 the same
+SIZES = [(1, 1, "bf16"), (7, 7, "bf16"), (8, 9, "bf16"), (519, 519, "bf16"), (8199, 8201, "bf16"), (32003, 32003, "bf16"),
+         (49159, 49159, "bf16"), (49161, 49162, "bf16"), (57353, 57353, "bf16"), (151669, 151936, "bf16"),
+         (188423, 188423, "bf16"), (188431, 188431, "bf16"), (3, 3, "f32"), (259, 261, "f32"), (4093, 4093, "f32"),
+         (77825, 77825, "f32"), (77831, 77832, "f32"), (151669, 151936, "f32")]
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("V,ld,dtype", SIZES)
+def test_loss_rows(V, ld, dtype, offset):
+    cfg, st, lg, act, behave, adv = _batch(V, ld, dtype, offset)
+    T = len(act)
+    seg = oracle.segments(st.T, st.step_tok_off, st.traj_step_off)
+    ref = oracle.loss_rows(to_np_logits(lg[:, :V].contiguous()), act.cpu().numpy(), behave.cpu().numpy(), None,
+                           adv.astype(np.float64), seg, cfg.G, norm=oracle.NORM_CONST_K, k=cfg.k, dual_clip_c=3.0)
+    gs = float(np.float32(1.0 / np.abs(ref.token_g).max()))
+    rel = 2.0 ** -8 if dtype == "bf16" else 0.0
+    for shift in (offset, offset + 1):  # dlogits at the logits' distance from a boundary, then at another
+        dl = torch.full((T * ld + 32,), 7.0, dtype=lg.dtype, device="cuda")[shift:shift + T * ld].view(T, ld)
+        loss, aux = _loss(cfg, st, lg, act, behave, adv, V, dl, gs)
+        assert abs(loss - ref.loss) <= LOSS_RTOL * np.abs(ref.token_contrib).sum()
+        assert np.abs(aux.token_logp.cpu().numpy() - ref.token_logp).max() <= LOGP_ATOL
+        assert aux.error_flags.item() == 0
+        r = ref.dlogits * gs
+        # the fp32 log2 in a row's log-sum-exp is good to about 2e-7 and |g| <= 1 here: all there is at V = 1
+        bound = rel * np.abs(r) + 1e-5 * np.abs(r).max(axis=1, keepdims=True) + 4e-7
+        err = np.abs(dl_to_f64(dl[:, :V]) - r)
+        assert (err <= bound).all(), (shift, float((err - bound).max()))
+        assert (dl[:, V:] == 7.0).all()  # columns past V are left alone
+
+
+def test_persistent_kernel_many_ragged_rows():
+    # several rows per workgroup, edges and vector counts changing from row to row, dlogits over the logits
+    V, T = 57353, 1200
+    cfg, st, lg, act, behave, adv = _batch(V, V, "bf16", 3, T=T, seed=8)
+    before = lg.clone()
+    seg = oracle.segments(st.T, st.step_tok_off, st.traj_step_off)
+    ref = oracle.loss_rows(to_np_logits(before), act.cpu().numpy(), behave.cpu().numpy(), None,
+                           adv.astype(np.float64), seg, cfg.G, norm=oracle.NORM_CONST_K, k=cfg.k, dual_clip_c=3.0)
+    gs = float(np.float32(1.0 / np.abs(ref.token_g).max()))
+    loss, aux = _loss(cfg, st, lg, act, behave, adv, V, lg, gs)
+    assert abs(loss - ref.loss) <= LOSS_RTOL * np.abs(ref.token_contrib).sum()
+    r = ref.dlogits * gs
+    err = np.abs(dl_to_f64(lg) - r)
+    assert (err <= 2.0 ** -8 * np.abs(r) + 1e-5 * np.abs(r).max(axis=1, keepdims=True)).all()
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("V,ld,dtype", SIZES)
+def test_logp_and_records(V, ld, dtype, offset):
+    _, _, lg, act, _, _ = _batch(V, ld, dtype, offset)
+    ref = oracle.logp_entropy(to_np_logits(lg[:, :V].contiguous()), act.cpu().numpy())
+    for entropy in (True, False):
+        logp, ent = grpo.grpo_token_logp(lg, act, V=V, entropy=entropy)
+        assert np.abs(logp.double().cpu().numpy() - ref.token_logp).max() <= LOGP_ATOL
+        if entropy:
+            assert (np.abs(ent.double().cpu().numpy() - ref.token_entropy)
+                    <= 2e-5 + 2e-5 * np.abs(ref.token_entropy)).all()
+    stats = grpo.grpo_vocab_shard_stats(lg, act, 0, V=V)
+    m, za, s = (x.cpu().numpy() for x in grpo.vocab_stats_fields(stats))
+    want = oracle.vocab_shard_stats(to_np_logits(lg[:, :V].contiguous()), act.cpu().numpy(), 0)
+    np.testing.assert_array_equal(m, want.m)
+    np.testing.assert_array_equal(za, want.za)
+    np.testing.assert_allclose(s, want.s, rtol=5e-6)
+
+
+@pytest.mark.parametrize("V,ld,dtype", [(1003, 1003, "bf16"), (1003, 1003, "f32"), (32003, 32003, "bf16"),
+                                        (57353, 57353, "bf16"), (77831, 77831, "f32"), (1000, 1000, "bf16")])
+def test_logits_masked_with_the_lowest_value(V, ld, dtype):
+    # all but the last 300 columns at the type's lowest value, as masks often are: they carry no probability, whole
+    # threads' shares of a row among them
+    cfg, st, lg, act, behave, adv = _batch(V, ld, dtype, 0)
+    lg[:, :V - 300] = torch.finfo(lg.dtype).min
+    act = act % 300 + (V - 300)
+    z = lg[:, V - 300:V].double()
+    lse = torch.logsumexp(z, 1)
+    want = z.gather(1, (act.long() - (V - 300))[:, None])[:, 0] - lse
+    logp, ent = grpo.grpo_token_logp(lg, act, V=V)
+    assert (logp.double() - want).abs().max().item() <= LOGP_ATOL
+    p = torch.exp(z - lse[:, None])
+    assert (ent.double() + (p * (z - lse[:, None])).sum(1)).abs().max().item() <= 4e-4
+    dl = torch.empty_like(lg)
+    _, aux = _loss(cfg, st, lg, act, want.float(), adv, V, dl, 1.0)
+    assert (aux.token_logp.double() - want).abs().max().item() <= LOGP_ATOL and aux.error_flags.item() == 0
+    assert (dl[:, :V - 300] == 0).all() and torch.isfinite(dl).all()
