@@ -53,19 +53,31 @@ __device__ __forceinline__ int gemm_col(int wn, int j, int lane) {
 // XCD-aware grouped tile order.  Workgroups are dispatched to the 8 XCDs round-robin, so workgroup b runs on
 // XCD b % 8; giving each XCD a contiguous range of logical tiles, ordered GM M-tiles at a time, lets the
 // workgroups sharing an XCD's L2 reuse each other's A and B slabs.  Launch a multiple of 8 workgroups.
-// Returns false past the last tile.
+// Returns false past the last tile.  With `layers`, that many such grids of tiles one after the other.
 template <int GM = 8>
-__device__ __forceinline__ bool gemm_tile_of(int bid, int nblocks, int tiles_m, int tiles_n, int& tm, int& tn) {
+__device__ __forceinline__ bool gemm_tile_of(int bid, int nblocks, int tiles_m, int tiles_n, int layers, int& tm,
+                                             int& tn, int& layer) {
   const int total = tiles_m * tiles_n;
   const int per = (nblocks + 7) / 8;
-  const int L = (bid % 8) * per + bid / 8;
-  if (L >= total) return false;
+  int L = (bid % 8) * per + bid / 8;
+  if (L >= total * layers) return false;
+  const int ly = L / total;
+  L -= ly * total;
   const int group = GM * tiles_n;
   const int g = L / group, first = g * GM;
   const int gm = min(tiles_m - first, GM);
-  tm = first + (L % group) % gm;
-  tn = (L % group) / gm;
+  // Divisions run on the vector unit: read back once here, the descriptors made from the tile stay in SGPRs.  Read
+  // back at each load instead, the v_readfirstlane stood fewer than the five wait states the ISA asks for before a
+  // load by inline asm (which the compiler does not check), and loads went out with a stale descriptor.
+  layer = __builtin_amdgcn_readfirstlane(ly);
+  tm = __builtin_amdgcn_readfirstlane(first + (L % group) % gm);
+  tn = __builtin_amdgcn_readfirstlane((L % group) / gm);
   return true;
+}
+template <int GM = 8>
+__device__ __forceinline__ bool gemm_tile_of(int bid, int nblocks, int tiles_m, int tiles_n, int& tm, int& tn) {
+  int layer;
+  return gemm_tile_of<GM>(bid, nblocks, tiles_m, tiles_n, 1, tm, tn, layer);
 }
 
 __device__ __forceinline__ g_u32x4 buffer_rsrc(const void* base, uint32_t bytes) {

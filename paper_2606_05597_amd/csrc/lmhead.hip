@@ -35,6 +35,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device.h"
@@ -579,16 +580,30 @@ __global__ __launch_bounds__(LmCfg::NT) void k_lm_dlogits(const DlogitsArgs p) {
 struct DhArgs {
   GemmArgs g;        // A = the pair buffer (M = T, K = the pair's width), B = W[:, pair] as [H, K], ldb = V
                      // (with PACKED: W packed as an H x V matrix)
-  float* acc;        // [Tp, H] fp32 accumulator (unused with a single chunk)
+  float* acc;        // [Tp, H] fp32 accumulator (unused with a single chunk); with splits > 1 their partials,
+                     // [splits][M, H]
   uint16_t* dh;      // [T, H] bf16 output
   int first, last;
+  int splits = 1;    // > 1 (not with PACKED): K cut into this many ranges of split_k columns, each range's product
+  int split_k = 0;   // a tile of its own, written to acc in fp32 (first = 1, last = 0)
 };
 
 // One tile of the dhidden product: block bid of nblocks (a multiple of 8, for the XCD order).
 template <bool PACKED = false>
-__device__ __forceinline__ void lm_dh_tile(const DhArgs& p, int bid, int nblocks, GemmSmem& sm) {
+__device__ __forceinline__ void lm_dh_tile(DhArgs p, int bid, int nblocks, GemmSmem& sm) {
   int tm, tn;
-  if (!gemm_tile_of(bid, nblocks, tiles_of(p.g.M), tiles_of(p.g.N), tm, tn)) return;
+  if (!PACKED && p.splits > 1) {
+    // the ranges one after the other: an XCD's tiles share a range's panels
+    int range;
+    if (!gemm_tile_of<8>(bid, nblocks, tiles_of(p.g.M), tiles_of(p.g.N), p.splits, tm, tn, range)) return;
+    const int k0 = range * p.split_k;
+    p.g.A += k0;
+    p.g.B += k0;
+    p.g.K = min(p.split_k, p.g.K - k0);
+    p.acc += (int64_t)range * p.g.M * p.g.N;
+  } else {
+    if (!gemm_tile_of(bid, nblocks, tiles_of(p.g.M), tiles_of(p.g.N), tm, tn)) return;
+  }
   const int m0 = tm * TILE, n0 = tn * TILE;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / LmCfg::WGN, wn = wave % LmCfg::WGN;
@@ -733,19 +748,30 @@ __global__ __launch_bounds__(LmCfg::NT) void k_lm_dh_dw(const DhDwArgs p) {
 
 // The token-blocked schedule's backward launch: the dhidden tiles (K = the whole vocabulary) first, then the dW
 // tiles (K = the block's rows).  A dhidden tile is then the longest unit by far; dispatched first, the long tiles
-// spread over the CUs and the many short dW tiles fill the time the last of them leave.  Both B operands (W and
-// D^T) come in the fragment-packed layout.
+// spread over the CUs and the many short dW tiles fill the time the last of them leave.  D^T comes in the
+// fragment-packed layout, W too when PACKED_W (dh_plan says when it doesn't).
 struct DhThenDwArgs {
   DhArgs dh;
   DwArgs dw;
   int dh_blocks;  // blocks [0, dh_blocks) take dhidden tiles, the rest dW tiles; a multiple of 8
 };
 
+template <bool PACKED_W>
 __global__ __launch_bounds__(LmCfg::NT) void k_lm_dh_then_dw(const DhThenDwArgs p) {
   __shared__ __attribute__((aligned(16))) GemmSmem sm;
   const int b = blockIdx.x;
-  if (b < p.dh_blocks) lm_dh_tile<true>(p.dh, b, p.dh_blocks, sm);
+  if (b < p.dh_blocks) lm_dh_tile<PACKED_W>(p.dh, b, p.dh_blocks, sm);
   else lm_dw_tile<true, true>(p.dw, b - p.dh_blocks, (int)gridDim.x - p.dh_blocks, sm);
+}
+
+// dhidden = the sum of the K ranges' fp32 partials [splits][n], in range order, rounded to bf16; n a multiple of 4.
+__global__ __launch_bounds__(256) void k_lm_dh_sum(const float* __restrict__ part, int splits, int64_t n,
+                                                   uint16_t* __restrict__ dh) {
+  for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < n; i += (int64_t)gridDim.x * 1024) {
+    f32x4 s = *reinterpret_cast<const f32x4*>(part + i);
+    for (int q = 1; q < splits; ++q) s += *reinterpret_cast<const f32x4*>(part + (int64_t)q * n + i);
+    *reinterpret_cast<u32x2*>(dh + i) = u32x2{pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3])};
+  }
 }
 
 // ---- D = g (softmax - onehot), bf16, as D and D^T: from fp32 logits (k_lm_block_d, a vocabulary shard's kept
@@ -1027,9 +1053,9 @@ static LmWs lm_ws_layout(int64_t T, int64_t H, int64_t V, int32_t C, int32_t n_t
   return l;
 }
 
-// A multiple of 8 workgroups covering every tile of an M x N output (see gemm_tile_of).
-static dim3 gemm_grid(int64_t M, int64_t N) {
-  const int64_t tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE);
+// A multiple of 8 workgroups covering every tile of an M x N output, `layers` times (see gemm_tile_of).
+static dim3 gemm_grid(int64_t M, int64_t N, int layers = 1) {
+  const int64_t tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE) * layers;
   return dim3((unsigned)((tiles + 7) / 8 * 8));
 }
 
@@ -1136,6 +1162,47 @@ static LmBlockWs lm_block_ws_layout(int64_t T, int64_t H, int64_t V, int32_t Tb,
   l.dt = o;   o = align_up(o + (size_t)packed_bytes(l.ldz, l.Tbp));
   l.total = o;
   return l;
+}
+
+// From this many tokens on, W is packed for the dhidden product as well as W^T for the forward one: the pack takes
+// 0.39 ms at 3,584 x 151,936 whatever T is, the packed core gains 2% of the dhidden tiles.  The whole call without /
+// with it at that W: T = 4,096 12.25 / 12.41 ms, 8,192 24.4 / 24.3, 16,384 47.9 / 47.7; both scale with W's size.
+constexpr int64_t kPackWMinT = 8192;
+
+// How a backward launch takes its dhidden tiles: K, the vocabulary, in `splits` ranges of split_k columns.
+struct DhPlan {
+  int splits, split_k;
+};
+
+// A dhidden tile walks the whole vocabulary, so a block of few rows has few tiles, each as long as all of the launch
+// should take: at 700 x 3,584 x 151,936 42 tiles of 2,374 slabs kept 42 CUs busy for 3.78 ms while the dW tiles were
+// done in under 1; the whole call took 5.3 ms and takes 2.9 (T = 64: 4.1 and 1.5; 1,500: 6.4 and 5.0; 4,096 and more
+// stay whole: 12.1).  The ranges are chosen for the shortest launch, counted in 64-deep slabs per CU (about 1.6 us
+// each): no shorter than the rounds of dhidden tiles, dispatched first, nor than all tiles spread evenly and one dW
+// tile more; a quarter of the time that the last round leaves CUs without a dhidden tile is taken as lost (the dW
+// tiles fill it, but the streams of D and W then run below the memory's rate); a tile's store counts 8 slabs, and the
+// partials (scratch_floats at most) are written, read and summed in a launch of their own.
+static DhPlan dh_plan(int64_t rows, int64_t H, int64_t V, int accumulate, int64_t scratch_floats, int n_cu) {
+  const int64_t nk = (V + 63) / 64, kb = (rows + 63) / 64;
+  const int64_t n_dh = (rows + TILE - 1) / TILE * ((H + TILE - 1) / TILE);
+  const int64_t n_dw = (V + TILE - 1) / TILE * ((H + TILE - 1) / TILE);
+  const double store = 8.0, dw = (double)kb + store * (accumulate ? 2 : 1);
+  DhPlan best{1, (int)(nk * 64)};
+  double best_t = 0.0;
+  for (int64_t s = 1; s <= 16 && s <= nk; ++s) {
+    const int64_t per = (nk + s - 1) / s, ranges = (nk + per - 1) / per;
+    if (ranges < s) continue;
+    if (s > 1 && s * rows * H > scratch_floats) break;
+    const int64_t n = n_dh * s;
+    const double dh = (double)per + store, rounds = (double)((n + n_cu - 1) / n_cu) * dh, share = (double)n * dh / n_cu;
+    double t = std::max(rounds, share + (double)n_dw * dw / n_cu + dw) + 0.25 * (rounds - share);
+    if (s > 1) t += 6.0 + (double)(s * rows * H) * 8.0 / 8e6;
+    if (s == 1 || t < best_t) {
+      best = DhPlan{(int)s, (int)(per * 64)};
+      best_t = t;
+    }
+  }
+  return best;
 }
 
 // The shard statistics call needs W^T of the shard and the pass-1 partials only.
@@ -1294,20 +1361,25 @@ extern "C" int fused_lmhead_grpo_blocked(const void* hidden, const void* w_lm, i
   lm_transpose(W16, h16, T, H, V, Tp, nullptr, hT, s);
   hipLaunchKernelGGL(k_pack_t, dim3((unsigned)((V + 63) / 64), (unsigned)((H + 63) / 64)), dim3(256), 0, s, W16, V,
                      (int)H, (int)V, WT);
-  hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)(packed_kb_count(V) / 4), (unsigned)((H + 31) / 32)), dim3(256), 0,
-                     s, W16, V, (int)H, (int)V, WP);
+  const bool pack_w = T >= kPackWMinT;
+  if (pack_w)
+    hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)(packed_kb_count(V) / 4), (unsigned)((H + 31) / 32)), dim3(256), 0,
+                       s, W16, V, (int)H, (int)V, WP);
+  const int n_cu = stream_cu_count(s);  // of the stream's device, which need not be the current one
+  if (n_cu < 1) return GRPO_ERR_HIP;
   if (hipGetLastError() != hipSuccess) return GRPO_ERR_HIP;
   const bool timed = aux && aux->hot_begin && aux->hot_end;
   if (timed && hipEventRecord(aux->hot_begin, s) != hipSuccess) return GRPO_ERR_HIP;
   const TokenArgs tok = make_token_args(V, actions, behave_logp, prox_logp, adv, p, w, L.loss, aux);
   const int n_blocks = (int)((T + L.Tbp - 1) / L.Tbp);
   auto rows_of = [&](int b) { return (int)(T - (int64_t)b * L.Tbp < L.Tbp ? T - (int64_t)b * L.Tbp : L.Tbp); };
+  auto rows64 = [](int rows) { return (rows + 63) / 64 * 64; };  // a block's rows of D and D^T, zeros past its own
   auto e_of = [&](int b) { return e16 + (size_t)(b & 1) * (size_t)(L.Tbp * L.ldz); };
   auto part_of = [&](int b) { return part + (size_t)(b & 1) * (size_t)(L.Tbp * L.n_tiles); };
   // block b's forward product (partials, logits into its buffer) and its rows' combine, on s
   auto forward = [&](int b) {
     const int64_t t0 = (int64_t)b * L.Tbp;
-    const int rows = rows_of(b), rows_p = (rows + TILE - 1) / TILE * TILE;
+    const int rows = rows_of(b);
     PartialArgs pa{};
     pa.g = GemmArgs{h16 + t0 * H, WT, H, 0, rows, (int)V, (int)H};
     pa.part = part_of(b);
@@ -1327,11 +1399,11 @@ extern "C" int fused_lmhead_grpo_blocked(const void* hidden, const void* w_lm, i
     ca.H = (int)H;
     ca.n_tiles = L.n_tiles;
     ca.t0 = (int)t0;
-    hipLaunchKernelGGL(k_lm_combine<true>, dim3((unsigned)rows_p), dim3(256), 0, s, ca);
+    hipLaunchKernelGGL(k_lm_combine<true>, dim3((unsigned)rows64(rows)), dim3(256), 0, s, ca);
   };
   // block b's D and D^T from its stored logits; `grid` workgroups (0: one per work item)
   auto dpass = [&](int b, hipStream_t st, int grid) {
-    const int rows_p = (rows_of(b) + TILE - 1) / TILE * TILE;
+    const int rows_p = rows64(rows_of(b));
     const BlockDArgs da{nullptr, e_of(b), part_of(b), L.n_tiles, rs + (int64_t)b * L.Tbp, D, DT, L.ldz, (int)V,
                         rows_p, 1};
     hipLaunchKernelGGL(k_lm_block_d16, dim3(block_d_grid(rows_p, L.ldz, grid)), dim3(256), 0, st, da);
@@ -1339,20 +1411,33 @@ extern "C" int fused_lmhead_grpo_blocked(const void* hidden, const void* w_lm, i
   // block b's dhidden rows = D W^T (K = V) and dW (+)= h^T D (K = the block's rows, zero-padded), on s
   auto backward = [&](int b) {
     const int64_t t0 = (int64_t)b * L.Tbp;
-    const int rows = rows_of(b), rows_p = (rows + TILE - 1) / TILE * TILE;
+    const int rows = rows_of(b);
+    const int acc_dw = (b > 0 || accumulate_dw) ? 1 : 0;
+    // the partials of a split go where the block's terms were, which its D pass has read
+    const DhPlan plan = dh_plan(rows, H, V, acc_dw, L.Tbp * L.ldz / 2, n_cu);
+    const bool packed = pack_w && plan.splits == 1;
     DhThenDwArgs ba;
-    ba.dh.g = GemmArgs{D, WP, L.ldz, 0, rows, (int)H, (int)V};
-    ba.dh.acc = nullptr;
+    ba.dh.g = packed ? GemmArgs{D, WP, L.ldz, 0, rows, (int)H, (int)V} : GemmArgs{D, W16, L.ldz, V, rows, (int)H, (int)V};
+    ba.dh.acc = reinterpret_cast<float*>(e_of(b));
     ba.dh.dh = dh16 + t0 * H;
     ba.dh.first = 1;
-    ba.dh.last = 1;
-    ba.dw.g = GemmArgs{hT + t0, DT, Tp, 0, (int)H, (int)V, rows_p};
+    ba.dh.last = plan.splits == 1;
+    ba.dh.splits = plan.splits;
+    ba.dh.split_k = plan.split_k;
+    ba.dw.g = GemmArgs{hT + t0, DT, Tp, 0, (int)H, (int)V, rows64(rows)};
     ba.dw.dw = dw_lm;
     ba.dw.V = V;
     ba.dw.c0 = 0;
-    ba.dw.accumulate = (b > 0 || accumulate_dw) ? 1 : 0;
-    ba.dh_blocks = (int)gemm_grid(rows, H).x;
-    hipLaunchKernelGGL(k_lm_dh_then_dw, dim3((unsigned)ba.dh_blocks + gemm_grid(H, V).x), dim3(LmCfg::NT), 0, s, ba);
+    ba.dw.accumulate = acc_dw;
+    ba.dh_blocks = (int)gemm_grid(rows, H, plan.splits).x;
+    const dim3 grid((unsigned)ba.dh_blocks + gemm_grid(H, V).x);
+    if (packed) hipLaunchKernelGGL(k_lm_dh_then_dw<true>, grid, dim3(LmCfg::NT), 0, s, ba);
+    else hipLaunchKernelGGL(k_lm_dh_then_dw<false>, grid, dim3(LmCfg::NT), 0, s, ba);
+    if (plan.splits > 1) {
+      const int64_t n = (int64_t)rows * H;
+      hipLaunchKernelGGL(k_lm_dh_sum, dim3((unsigned)std::min<int64_t>((n + 1023) / 1024, 4096)), dim3(256), 0, s,
+                         ba.dh.acc, plan.splits, n, ba.dh.dh);
+    }
   };
   const bool two = s_aux && s_aux != s && n_blocks > 1;
   if (!two) {
@@ -1367,8 +1452,6 @@ extern "C" int fused_lmhead_grpo_blocked(const void* hidden, const void* w_lm, i
     // CU, so that each CU holds one of each: the forward product's workgroup leaves room in LDS and registers
     // for one D-pass workgroup.  ev_c: block b's rows are combined and the previous backward launch (the last
     // reader of D, D^T) is done; ev_d: block b's D pass is done.
-    const int n_cu = stream_cu_count(s);  // of the streams' device, which need not be the current one
-    if (n_cu < 1) return GRPO_ERR_HIP;
     hipEvent_t ev_c = nullptr, ev_d = nullptr;
     if (hipEventCreateWithFlags(&ev_c, hipEventDisableTiming) != hipSuccess) return GRPO_ERR_HIP;
     if (hipEventCreateWithFlags(&ev_d, hipEventDisableTiming) != hipSuccess) {

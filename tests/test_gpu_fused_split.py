@@ -1,0 +1,44 @@
+"""The token-blocked fused path on few rows, where the dhidden product runs in ranges of the vocabulary whose fp32
+partials are summed afterwards: a last range that is short, one that ends inside a 64-deep slab, H not a multiple of the
+tile, several blocks on one and on two streams (the partials lie in the block's own terms).  The oracle and the gates
+are those of tests/test_gpu_fused.py."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2606_05597_amd as grpo
+from oracle import fused
+from tests.gpu_parity import check_fused_loss, gpu_norm
+from tests.test_gpu_fused import bits, check_dh
+from tests.test_gpu_fused_edges import edge_batch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,H,V,block,streams", [(1, 64, 20000, 8192, 1), (130, 64, 20000, 8192, 1),
+                                                 (300, 192, 8200, 8192, 1), (600, 192, 8200, 256, 1),
+                                                 (600, 192, 8200, 256, 2), (513, 320, 4104, 512, 2)])
+def test_split_dhidden(T, H, V, block, streams):
+    e = edge_batch(T, H, V, seed=T + H + V)
+    A32 = oracle.advantages(e["rewards"], e["G"]).astype(np.float32)
+    seg = oracle.segments(T, e["sto"], e["tso"])
+    ref = fused.fused_loss(bits(e["hidden"]), bits(e["W"]), e["actions"], e["behave"], None, A32.astype(np.float64),
+                           seg, e["G"], norm=oracle.NORM_CONST_K, k=4.0, dual_clip_c=3.0)
+    dw0 = torch.randn((H, V), device="cuda", generator=torch.Generator("cuda").manual_seed(9)) * 1e-3
+    loss, dh, dW = grpo.fused_lmhead_grpo_blocked(
+        e["hidden"], e["W"], torch.from_numpy(e["actions"]).cuda(), torch.from_numpy(e["behave"]).cuda(),
+        torch.from_numpy(A32).cuda(), torch.from_numpy(e["sto"]).cuda(), torch.from_numpy(e["tso"]).cuda(), e["G"],
+        token_block=block, norm=gpu_norm(oracle.NORM_CONST_K), k=4.0, dual_clip_c=3.0, dw_lm=dw0.clone(),
+        accumulate_dw=True, aux_stream=torch.cuda.Stream() if streams == 2 else None)
+    torch.cuda.synchronize()
+    check_fused_loss(loss.item(), ref.rows.token_contrib, "loss")
+    W64, h64 = fused.as_f64(bits(e["W"])), fused.as_f64(bits(e["hidden"]))
+    check_dh(dh.float().cpu().numpy().astype(np.float64), ref.dhidden, ref.rows.dlogits, W64)
+    got = dW.cpu().numpy().astype(np.float64) - dw0.cpu().numpy().astype(np.float64)
+    # the product's own bound, the rounding of fp16 terms below 2^-14 (2^-25 of |g|: at V = 20,000 many are) and one
+    # fp32 rounding of dw0 + dW
+    D = np.abs(ref.rows.dlogits) + 2.0 ** -18 * np.abs(ref.rows.token_g)[:, None]
+    bound = 2.0 ** -7 * (np.abs(h64).T @ D) + 2.0 ** -23 * np.abs(dw0.cpu().numpy())
+    err = np.abs(got - ref.dW)
+    assert (err <= bound + 1e-30).all(), float((err / (bound + 1e-30)).max())
