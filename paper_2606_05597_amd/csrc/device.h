@@ -12,7 +12,8 @@ namespace grpo {
 struct WsHeader {
   int32_t flags;      // GRPO_FLAG_* of this call (set by the segment pass, OR-ed by the row pass)
   uint32_t done;      // reduction workgroups finished (last-block pattern)
-  int64_t counts[4];  // eps-clip cut, dual-clip cut, ratio outside the clip range, valid tokens
+  int64_t counts[4];  // [0]: eps-clip cut, dual-clip cut; [1]: ratio outside the clip range, valid tokens (each pair
+                      // the low and high 32 bits)
 };
 
 constexpr float kLog2e = 1.4426950408889634f;
