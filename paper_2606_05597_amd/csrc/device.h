@@ -375,10 +375,22 @@ __device__ __forceinline__ u32x4 vec_dlogits(const u32x4& x, const RowScale& rs,
   return o;
 }
 
+// ---- a row through a buffer descriptor ----------------------------------------
+// Buffer resources cover exactly one row: every access is a 32-bit
+// lane offset (tid*16) plus a constant per-vector offset, and the hardware
+// range check returns 0 for loads past the row and drops such stores.
+constexpr uint32_t kRsrcWord3 = 0x00020000u;  // raw buffer, 32-bit data format
+constexpr int kStream = 2;                    // non-temporal cache policy for streamed rows
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, kRsrcWord3);
+}
+
+
 // ---- rows that start at any element -------------------------------------------
 // A row of V elements at any element-aligned address: `head` elements up to the first 16-byte boundary (fewer than a
 // vector holds), `nvec` whole 16-byte vectors, `tail` elements after them.  The vectors run through the same code as
-// an aligned row's; the at most 14 edge elements (6 in fp32) go to the first threads of the workgroup, one each.
+// an aligned row's; the at most 14 edge elements (6 of fp32 log-prob and shard rows) go to the first threads of the workgroup, one each.
 // RAG = false: the caller knows that every row is whole aligned vectors, and the split is constant.
 // HBM-bound like the aligned rows.  Reading a ragged row element by element, three times, cost four times as much:
 // the loss and dlogits of bf16 6,007 x 151,669 (columns padded to 151,936) took 3.16 ms and take 0.73 (5.0 TB/s),

@@ -34,6 +34,11 @@ hipError_t launch_shard_rows(const void* logits, void* dlogits, grpo_dtype dt, i
                              int64_t v_begin, const grpo_vocab_stats* stats, int n_shards, const TokenArgs& tok,
                              hipStream_t s);
 
+// One workgroup per row of whole aligned fp32 vectors, the row read twice: its sum, the token epilogue, its dlogits
+// (nullable = forward only).
+hipError_t launch_rows_twice(const void* logits, void* dlogits, int64_t T, int64_t ld, const TokenArgs& tok,
+                             hipStream_t s);
+
 // Reduces the per-token loss contributions: per trajectory, then over
 // trajectories, both in a fixed order; writes loss_out and the aux outputs.
 hipError_t launch_reduce(int64_t T, int32_t n_traj, char* ws, const LossWs& L, double* loss_out,

@@ -182,6 +182,139 @@ __global__ __launch_bounds__(NT) void k_logp_vec(const LogpArgs a) {
   if (tid == 0) row_out<Tin>(a, t, M, S, Tsum, act_ok ? (double)sh_za : 0.0, act_ok);
 }
 
+// ---- loss and dlogits of rows that no kernel holds -------------------------------
+struct TwiceArgs {
+  const void* logits;
+  void* dlogits;
+  int64_t ld;
+  int T;
+  TokenArgs tok;
+};
+
+// One workgroup per row of whole aligned vectors: the row's sum as k_logp_vec forms it for a record (the same terms in
+// the same order, so that the results are those of the two launches to the bit), the token epilogue, then dlogits.  A
+// thread's first HR vectors stay in registers and the next HL in LDS (rows have more than that); the rest is read a
+// second time, backwards, the end of the row from the L2 and the most of it from the memory-side cache: at two
+// workgroups per CU, which the registers and the LDS are sized for, the rows in flight are less than its 256 MB.
+// HBM-bound.  fp32 loss and dlogits, in two launches / here: 6,000 x 151,936 2.01 / 1.48 ms (4.9 TB/s of the row read and
+// written once), 8,000 x 100,000 1.68 / 1.22, 3,000 x 262,144 1.62 / 1.32, 800 x 1,000,000 1.89 / 1.78, 64 x 151,936
+// 0.078 / 0.042; with nothing held 1.60 at 151,936, with more workgroups per CU 1.66 to 2.0.
+template <typename Tin, int NT, int U, int HR, int HL>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_rows_twice(const TwiceArgs a) {
+  constexpr int EPV = 16 / sizeof(Tin), NW = NT / 64, H = HR + HL;
+  static_assert(HR % U == 0 && HL % U == 0, "whole chunks");
+  __shared__ u32x4 stage[HL * NT];
+  __shared__ float sh_m[NW];
+  __shared__ double sh_s[NW], sh_t[NW];
+  __shared__ float sh_za;
+  __shared__ RowScale sh_rs;
+  const int t = blockIdx.x, tid = threadIdx.x;
+  const int nvec = (int)(a.tok.V / EPV);
+  constexpr int VB = NT * 16;
+  const int voff = tid * 16;
+  const char* row = reinterpret_cast<const char*>(static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld);
+  // a vector of the row; past its end, the last one, which is then left out
+  auto at = [&](int vi) { return reinterpret_cast<const u32x4*>(row + (uint32_t)min(vi, nvec - 1) * 16u); };
+  const TokenIn in = token_load(a.tok, t);
+  const bool act_ok = in.act >= 0 && in.act < a.tok.V;
+  const RowSplit sp{0, nvec, 0};
+  int act_lane;
+  const int act_vec = vec_of<Tin>(sp, act_ok ? in.act : -1, act_lane);
+  float m = kShiftMin, s = 0.f, tt = 0.f;
+  u32x4 hold[HR], x[U], y[U];
+#pragma unroll
+  for (int q = 0; q < HR; ++q) 
+    hold[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row + q * VB + (uint32_t)voff));
+  auto load = [&](u32x4 (&v)[U], int q) {  // vectors q .. q + U - 1 of the thread
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = *at((q + u) * NT + tid);
+  };
+  auto sum = [&](const u32x4* v, int q, bool whole) {
+    const int base = q * NT + tid;
+    float cm = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int vi = base + u * NT;
+      if (whole || vi < nvec) {
+        cm = vec_max<Tin>(v[u], cm);
+        if (vi == act_vec) sh_za = elem<Tin>(v[u], act_lane);
+      }
+    }
+    rescale<false>(m, cm, s, tt);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int vi = base + u * NT;
+      if (whole || vi < nvec) {
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) fold<false>(elem<Tin>(v[u], e), -m * kLog2e, s, tt);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load(x, HR);
+#pragma unroll
+  for (int q = 0; q < HR; q += U) sum(hold + q, q, true);
+#pragma unroll 1
+  for (int q = 0; q < HL; q += 2 * U) {  // two chunks in flight, in turn
+    load(y, HR + q + U);
+#pragma unroll
+    for (int u = 0; u < U; ++u) stage[(q + u) * NT + tid] = x[u];
+    sum(x, HR + q, true);
+    load(x, HR + q + 2 * U);
+#pragma unroll
+    for (int u = 0; u < U; ++u) stage[(q + U + u) * NT + tid] = y[u];
+    sum(y, HR + q + U, true);
+  }
+  const int nv = (nvec + NT - 1) / NT;
+#pragma unroll 1
+  for (int q = H; q < nv; q += 2 * U) {
+    load(y, q + U);
+    sum(x, q, false);
+    load(x, q + 2 * U);
+    sum(y, q + U, false);
+  }
+  double M, S, Tsum;
+  block_combine3<NW>(m, s, tt, sh_m, sh_s, sh_t, M, S, Tsum);  // its barrier publishes sh_za
+  if (tid == 0) {
+    if (isnan(M) || isnan(S) || M == INFINITY) atomicOr(&a.tok.hdr->flags, GRPO_FLAG_NONFINITE);
+    sh_rs = token_finish(a.tok, t, in, row_lse(M, S), act_ok ? (double)sh_za : 0.0);
+  }
+  __syncthreads();
+  if (!a.dlogits) return;
+  const RowScale rs = sh_rs;
+  const uint32_t smask = sign_mask<Tin>(rs);
+  int act_l;
+  const int act_v = vec_of<Tin>(sp, rs.act, act_l);
+  const __amdgpu_buffer_rsrc_t dst = row_rsrc(static_cast<Tin*>(a.dlogits) + (int64_t)t * a.ld, nvec * 16);
+  auto put = [&](const u32x4& v, int q) {
+    __builtin_amdgcn_raw_buffer_store_b128(vec_dlogits<Tin>(v, rs, smask, q * NT + tid == act_v, act_l), dst, voff,
+                                           q * VB, kStream);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 1" ::: "memory");  // the store has read its data before its registers are reused
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr int U2 = 8;
+#pragma unroll 1
+  for (int q = H + (nv - H + U2 - 1) / U2 * U2 - U2; q >= H; q -= U2) {
+    u32x4 z[U2];
+#pragma unroll
+    for (int u = 0; u < U2; ++u) z[u] = __builtin_nontemporal_load(at((q + u) * NT + tid));
+#pragma unroll
+    for (int u = 0; u < U2; ++u) put(z[u], q + u);
+  }
+#pragma unroll 1
+  for (int q = 0; q < HL; ++q) put(stage[q * NT + tid], HR + q);
+#pragma unroll
+  for (int q = 0; q < HR; ++q) put(hold[q], q);
+}
+
+hipError_t launch_rows_twice(const void* logits, void* dlogits, int64_t T, int64_t ld, const TokenArgs& tok,
+                             hipStream_t s) {
+  const TwiceArgs a{logits, dlogits, ld, (int)T, tok};
+  hipLaunchKernelGGL((k_rows_twice<float, 256, 4, 36, 16>), dim3((unsigned)T), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 __global__ void k_clear_flag(int32_t* f) { *f = 0; }
 
 typedef void (*LogpKernel)(const LogpArgs);

@@ -11,21 +11,26 @@
 //                   while row t's dlogits are written: part of each row lives
 //                   in LDS (global_load_lds), the rest in registers.
 //  k_rows_resident  shorter rows: one workgroup per row, several per CU.
-//  Rows that are not whole 16-byte vectors (odd vocabularies, strides or
+//  bf16 rows that are not whole 16-byte vectors (odd vocabularies, strides or
 //  addresses) take the same kernels, split at the 16-byte boundaries into
 //  vectors and at most 14 edge elements (device.h RowSplit).
-//  two passes       rows too long for either (fp32 beyond 77,824
-//                   columns, bf16 beyond 188,416): each row reduced to a
-//                   record (logp.hip), then the record turned into the token
-//                   epilogue and the row's dlogits (vocab.hip); the row is
-//                   read twice.
-//  k_rows_generic   dlogits at another distance from a 16-byte boundary than the
-//                   logits: element loads, three sweeps.
+//  k_rows_stream    bf16 rows that one CU cannot hold (beyond 188,416 columns), up
+//                   to 4 MiB: persistent, most of the row held, the rest read a
+//                   second time from the caches.
+//  k_rows_twice     (logp.hip) fp32 rows beyond 77,824 columns: one workgroup per
+//                   row, part of it held, the rest read a second time.
+//  two passes       longer rows: each row reduced to a record (logp.hip), then
+//                   the record turned into the token epilogue and the row's
+//                   dlogits (vocab.hip); the row is read twice.
+//  k_rows_elements  fp32 rows that are not whole 16-byte vectors, and rows whose
+//                   dlogits lie at another distance from a 16-byte boundary than
+//                   their logits: element loads.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "device.h"
 #include "launch.h"
@@ -40,7 +45,8 @@ struct RowArgs {
   void* dlogits;  // nullable: forward only
   int64_t ld;     // row stride in elements
   int T;
-  int chunk;      // k_rows_pipe: consecutive rows a workgroup takes at a time (>= 1) in rows [0, r0)
+  int chunk;      // k_rows_pipe: consecutive rows a workgroup takes at a time (>= 1) in rows [0, r0); k_rows_elements:
+                  // whether the dynamic LDS holds a row
   int r0;         // k_rows_pipe: a multiple of chunk * gridDim.x
   int chunk2;     // k_rows_pipe: rows [r0, T) go chunk2 at a time, one chunk per workgroup (>= 1)
   TokenArgs tok;
@@ -174,16 +180,6 @@ __device__ __forceinline__ void block_combine_all(float m, float s, float* sh_m,
 }
 
 // ---- persistent pipelined kernel for long bf16 rows ----------------------------
-// Buffer resources cover exactly one row (V*2 bytes): every access is a 32-bit
-// lane offset (tid*16) plus a constant per-vector offset, and the hardware
-// range check returns 0 for loads past the row and drops such stores.
-constexpr uint32_t kRsrcWord3 = 0x00020000u;  // raw buffer, 32-bit data format
-constexpr int kStream = 2;                    // non-temporal cache policy for streamed rows
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, kRsrcWord3);
-}
-
 // 16 bytes per lane from the buffer (rsrc, voff + soff) into LDS at lds_base + 16 * lane, non-temporal.
 // Inline asm: the compiler's own handling of LDS DMA would hold every LDS read back until all LDS DMA in
 // flight has landed; the kernel orders them with explicit waits instead.  M0 carries the LDS address;
@@ -404,6 +400,205 @@ __global__ __launch_bounds__(1024) void k_rows_pipe(const RowArgs a) {
   }
 }
 
+// ---- persistent kernel for rows that one CU cannot hold --------------------------
+// As k_rows_pipe (one workgroup of 1024 threads per CU, 16-byte vectors j * 1024 + tid), with the row in three parts:
+// vectors 0 .. NP-1 in LDS, the next NR in registers, and the rest streamed, U at a time, through one more set of
+// registers.  The streamed part is read twice: forwards for (max, sum exp), then, beginning with the last U vectors,
+// which are still there, backwards for dlogits.  HBM-bound: the second read finds its vectors in the memory-side
+// cache, since all CUs together have read less than its 256 MB in between (kStreamMaxRow).
+// A row fills the first two parts (at least NP + NR vectors and one element more per thread).
+// Every load and store is issued whatever the row's length (stores past it are dropped by the range check of the row's
+// descriptor), so that the wait for the LDS part counts the same operations on every row.
+template <typename Tin, int NP, int NR, int U, bool RAG>
+__global__ __launch_bounds__(1024) void k_rows_stream(const RowArgs a) {
+  constexpr int NT = 1024, NW = NT / 64, VB = NT * 16, NH = NP + NR;
+  __shared__ __attribute__((aligned(16))) u32x4 stage[NP * NT];
+  __shared__ float sh_m[NW];
+  __shared__ double sh_s[NW];
+  __shared__ float sh_za;
+  __shared__ TokenIn sh_in;  // inputs of the row about to start (wave 1 loads them during the previous row)
+  const int wv = threadIdx.x >> 6;
+  const Tin* logits = static_cast<const Tin*>(a.logits);
+  Tin* dlogits = static_cast<Tin*>(a.dlogits);
+  auto split = [&](int r) { return row_split<Tin, RAG>(logits + (int64_t)r * a.ld, a.tok.V); };
+  auto source = [&](int r, const RowSplit& sp) { return row_rsrc(logits + (int64_t)r * a.ld + sp.head, sp.nvec * 16); };
+  const uint32_t lds_stage =
+      (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) u32x4*)stage) + wv * 64 * 16;
+  auto stage_row = [&](int r, const RowSplit& sp, int voff) {
+    const u32x4 src = row_rsrc_words(logits + (int64_t)r * a.ld + sp.head, (uint32_t)sp.nvec * 16u);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) dma16_nt(lds_stage + j * NT * 16, voff, j * VB, src);
+  };
+  u32x4 reg[NR], x[U];
+  auto load_batch = [&](int r, const RowSplit& sp, int b, int tid) {  // past the row's end: the last vector, left out
+    const char* row = reinterpret_cast<const char*>(logits + (int64_t)r * a.ld + sp.head);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      x[u] = *reinterpret_cast<const u32x4*>(row + (uint32_t)min((NH + b * U + u) * NT + tid, sp.nvec - 1) * 16u);
+  };
+  const int nb = (int)((a.tok.V / (16 / (int)sizeof(Tin)) + NT - 1) / NT - NH + U - 1) / U;  // batches, at least one
+
+  // rows to workgroups as in k_rows_pipe
+  const int C = a.chunk, R0 = a.r0, C2 = a.chunk2;
+  auto next_row = [&](int r) {
+    const int q = r + 1;
+    if (r < R0) {
+      if (q % C != 0) return q;
+      const int nq = q + ((int)gridDim.x - 1) * C;
+      return nq < R0 ? nq : min(R0 + (int)blockIdx.x * C2, a.T);
+    }
+    return ((q - R0) % C2 != 0 && q < a.T) ? q : a.T;
+  };
+  int t = R0 > 0 ? (int)blockIdx.x * C : R0 + (int)blockIdx.x * C2;
+  if (t >= a.T) return;
+  float ez = -INFINITY;  // RAG: the thread's edge element of row t
+  auto load_edge = [&](int r, const RowSplit& sp, int tid) {
+    const int c = edge_col<Tin>(sp, tid);
+    return c >= 0 ? load_elem(logits + (int64_t)r * a.ld + c) : -INFINITY;
+  };
+  {
+    const RowSplit sp = split(t);
+    const __amdgpu_buffer_rsrc_t src = source(t, sp);
+    const int voff = threadIdx.x * 16;
+    if constexpr (RAG) ez = load_edge(t, sp, threadIdx.x);
+    if (threadIdx.x == 64) sh_in = token_load(a.tok, t);
+    stage_row(t, sp, voff);
+#pragma unroll
+    for (int q = 0; q < NR; ++q) reg[q] = __builtin_amdgcn_raw_buffer_load_b128(src, voff, (NP + q) * VB, kStream);
+    load_batch(t, sp, 0, threadIdx.x);
+    wait_vmcnt<NR + U>();  // this wave's LDS part of row t has landed; the others may still be in flight
+  }
+
+  for (int t_next = 0; t < a.T; t = t_next) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // nothing derived from it is hoisted out of the row loop
+    const int voff = tid * 16;
+    const RowSplit sp = split(t);
+    const int tn = next_row(t);
+    t_next = tn;
+    lds_barrier();  // every wave's LDS part of row t has landed, and sh_in holds row t's inputs
+    const TokenIn in = sh_in;
+    const bool act_ok = in.act >= 0 && in.act < a.tok.V;
+    int act_lane;
+    const int act_vec = vec_of<Tin>(sp, act_ok ? in.act : -1, act_lane);
+    const int ecol = RAG ? edge_col<Tin>(sp, tid) : -1;
+
+    // (max, sum exp) over the LDS part, then the register part, each with a shift of its own, then the batches
+    float m = kShiftMin, s = 0.f;
+    auto raise = [&](float mn) {
+      s *= __builtin_amdgcn_exp2f((m - mn) * kLog2e);
+      m = mn;
+    };
+    {
+      float mn = m;
+#pragma unroll 1
+      for (int j = 0; j < NP; ++j) {
+        const u32x4 v = stage[j * NT + tid];
+        mn = vec_max<Tin>(v, mn);
+        if (j * NT + tid == act_vec) sh_za = vec_elem<Tin>(v, act_lane);
+      }
+      m = mn;
+#pragma unroll 1
+      for (int j = 0; j < NP; ++j) s += vec_sumexp<Tin>(stage[j * NT + tid], -m * kLog2e);
+    }
+    {
+      float mn = m;
+#pragma unroll
+      for (int q = 0; q < NR; ++q)
+      {
+        mn = vec_max<Tin>(reg[q], mn);
+        if ((NP + q) * NT + tid == act_vec) sh_za = vec_elem<Tin>(reg[q], act_lane);
+      }
+      if constexpr (RAG) {
+        mn = fmaxf(mn, ez);
+        if (act_ok && ecol == in.act) sh_za = ez;
+      }
+      raise(mn);
+      fresh(reg);
+#pragma unroll
+      for (int q = 0; q < NR; ++q)
+      {
+        s += vec_sumexp<Tin>(reg[q], -m * kLog2e);
+        __builtin_amdgcn_sched_barrier(0);  // else every exponential is issued first and its results spill
+      }
+      if constexpr (RAG) s += __builtin_amdgcn_exp2f(fmaf(ez, kLog2e, -m * kLog2e));  // no edge: exp2(-inf) = 0
+    }
+#pragma unroll 1
+    for (int b = 0; b < nb; ++b) {
+      if (b > 0) load_batch(t, sp, b, tid);
+      float mn = m;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int vi = (NH + b * U + u) * NT + tid;
+        if (vi < sp.nvec) {
+          mn = vec_max<Tin>(x[u], mn);
+          if (vi == act_vec) sh_za = vec_elem<Tin>(x[u], act_lane);
+        }
+      }
+      raise(mn);
+      fresh(x);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+      {
+        if ((NH + b * U + u) * NT + tid < sp.nvec) s += vec_sumexp<Tin>(x[u], -m * kLog2e);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+
+    double M, S;
+    block_combine_all<NW>(m, s, sh_m, sh_s, M, S);  // barrier: sh_za is visible, every lane holds (M, S)
+    TokenEval ev;
+    const RowScale rs = token_eval(a.tok, in, row_lse(M, S), (double)sh_za, ev);
+    if (tid == 0) token_store(a.tok, t, in, ev);
+    if (tid == 64) sh_in = token_load(a.tok, tn < a.T ? tn : t);
+
+    const uint32_t smask = sign_mask<Tin>(rs);
+    int act_l;
+    const int act_v = vec_of<Tin>(sp, rs.act, act_l);
+    // forward only: a zero-sized destination, so the range check drops every store
+    const bool write = dlogits != nullptr;
+    Tin* drow = write ? dlogits + (int64_t)t * a.ld : nullptr;
+    const __amdgpu_buffer_rsrc_t dst = row_rsrc(write ? (const void*)(drow + sp.head) : (const void*)logits, write ? sp.nvec * 16 : 0);
+    // each store is followed by two wait states, as in k_rows_pipe
+    auto put = [&](const u32x4& v, int j) {
+      __builtin_amdgcn_raw_buffer_store_b128(vec_dlogits<Tin>(v, rs, smask, j * NT + tid == act_v, act_l), dst, voff,
+                                             j * VB, kStream);
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_nop 1" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    fresh(x);
+#pragma unroll 1
+    for (int b = nb - 1; b >= 0; --b) {
+      if (b < nb - 1) load_batch(t, sp, b, tid);
+#pragma unroll
+      for (int u = 0; u < U; ++u) put(x[u], NH + b * U + u);
+    }
+#pragma unroll 1
+    for (int j = 0; j < NP; ++j)
+      __builtin_amdgcn_raw_buffer_store_b128(
+          vec_dlogits<Tin>(stage[j * NT + tid], rs, smask, j * NT + tid == act_v, act_l), dst, voff, j * VB, kStream);
+    const RowSplit spn = split(tn < a.T ? tn : t);
+    if constexpr (RAG) {
+      if (write && ecol >= 0) store_elem(drow + ecol, elem_dlogits(ez, rs, ecol, rs.act));
+      ez = load_edge(tn < a.T ? tn : t, spn, tid);
+    }
+    lds_barrier();  // every wave is done reading stage[] (the stores read registers)
+    // past the last row: a zero-sized source, every load returns 0
+    if (tn < a.T) stage_row(tn, spn, voff);
+    const __amdgpu_buffer_rsrc_t nxt =
+        row_rsrc(logits + (int64_t)(tn < a.T ? tn : t) * a.ld + spn.head, tn < a.T ? spn.nvec * 16 : 0);
+    fresh(reg);
+#pragma unroll
+    for (int q = 0; q < NR; ++q) put(reg[q], NP + q);
+#pragma unroll
+    for (int q = 0; q < NR; ++q) reg[q] = __builtin_amdgcn_raw_buffer_load_b128(nxt, voff, (NP + q) * VB, kStream);
+    load_batch(tn < a.T ? tn : t, spn, 0, tid);
+    // 2 NR + U operations were issued after the LDS part of row tn: this returns once that part has landed
+    wait_vmcnt<2 * NR + U>();
+  }
+}
+
 // ---- register-resident row kernel -------------------------------------------
 // NT threads per row, NV 16-byte vectors per thread: V/EPV <= NT*NV.  RAG: rows that
 // are not whole aligned vectors (RowSplit), otherwise they are (checked on the host).
@@ -475,36 +670,69 @@ __global__ __launch_bounds__(NT) void k_rows_resident(const RowArgs a) {
   if (RAG && ecol >= 0) store_elem(drow + ecol, elem_dlogits(ez, rs, ecol, rs.act));
 }
 
-// ---- generic row kernel ------------------------------------------------------
-// Any V, ld and element alignment: element-wise loads, the row read three
-// times (max, sum, dlogits).  Used when the vector kernels do not apply: dlogits
-// at another distance from a 16-byte boundary than the logits.
+// ---- element row kernel --------------------------------------------------------
+// Any V, ld and element alignment, thread k of 256 on columns k, k + 256, ...: fp32 rows that are not whole aligned
+// vectors, and rows whose dlogits lie at another distance from a 16-byte boundary than their logits.  Three sweeps
+// (max, sum, dlogits) with U elements in flight; a row that fits the workgroup's dynamic LDS (stage_row) is read from
+// memory once and from there afterwards.  A thread's terms are summed one after the other in column order.
+// Bound by the element accesses' rate and, unstaged, by the re-reads.  fp32 loss and dlogits with one element in flight
+// and every sweep from memory / here: 30,000 x 9,001 0.94 / 0.41 ms (5.3 TB/s), 20,000 x 19,003 1.32 / 0.71, 10,000 x
+// 32,003 1.26 / 0.80, 6,000 x 151,669 3.77 / 3.23.
 template <typename Tin>
-__global__ __launch_bounds__(256) void k_rows_generic(const RowArgs a) {
-  constexpr int NT = 256, NW = NT / 64;
+__global__ __launch_bounds__(256) void k_rows_elements(const RowArgs a) {
+  constexpr int NT = 256, NW = NT / 64, U = 16;
+  extern __shared__ __attribute__((aligned(16))) char dyn[];
+  Tin* stage = reinterpret_cast<Tin*>(dyn);
   __shared__ float sh_m[NW];
   __shared__ double sh_s[NW];
   __shared__ RowScale sh_rs;
   const int t = blockIdx.x, tid = threadIdx.x;
+  const int64_t V = a.tok.V;
   const Tin* row = static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld;
+  const bool staged = a.chunk != 0;
   const TokenIn in = token_load(a.tok, t);
+  // f(column, logit) for the thread's columns in order
+  auto sweep = [&](auto from_lds, auto f) {
+    for (int64_t base = tid; base < V; base += NT * U) {
+      Tin z[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t v = base + u * NT;
+        if (v < V) z[u] = from_lds ? stage[v] : row[v];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t v = base + u * NT;
+        if (v < V) f(v, z[u]);
+      }
+    }
+  };
   float m = -INFINITY;
-  for (int64_t v = tid; v < a.tok.V; v += NT) m = fmaxf(m, load_elem(row + v));
+  if (staged)
+    sweep(std::false_type(), [&](int64_t v, Tin z) {
+      stage[v] = z;  // read back by the same thread
+      m = fmaxf(m, load_elem(&z));
+    });
+  else
+    sweep(std::false_type(), [&](int64_t, Tin z) { m = fmaxf(m, load_elem(&z)); });
   const float nmb = (m == -INFINITY) ? 0.f : -m * kLog2e;
   float s = 0.f;
-  for (int64_t v = tid; v < a.tok.V; v += NT) s += __builtin_amdgcn_exp2f(fmaf(load_elem(row + v), kLog2e, nmb));
+  auto add = [&](int64_t, Tin z) { s += __builtin_amdgcn_exp2f(fmaf(load_elem(&z), kLog2e, nmb)); };
+  if (staged) sweep(std::true_type(), add);
+  else sweep(std::false_type(), add);
   double M, S;
   block_combine<NW>(m, s, sh_m, sh_s, M, S);
   if (tid == 0) {
-    const bool ok = in.act >= 0 && (int64_t)in.act < a.tok.V;
+    const bool ok = in.act >= 0 && (int64_t)in.act < V;
     sh_rs = token_finish(a.tok, t, in, row_lse(M, S), ok ? (double)load_elem(row + in.act) : 0.0);
   }
   __syncthreads();
   if (!a.dlogits) return;
   const RowScale rs = sh_rs;
   Tin* drow = static_cast<Tin*>(a.dlogits) + (int64_t)t * a.ld;
-  for (int64_t v = tid; v < a.tok.V; v += NT)
-    store_elem(drow + v, elem_dlogits(load_elem(row + v), rs, (int)v, rs.act));
+  auto put = [&](int64_t v, Tin z) { store_elem(drow + v, elem_dlogits(load_elem(&z), rs, (int)v, rs.act)); };
+  if (staged) sweep(std::true_type(), put);
+  else sweep(std::false_type(), put);
 }
 
 // ---- dispatch ------------------------------------------------------------------
@@ -512,13 +740,13 @@ typedef void (*RowKernel)(const RowArgs);
 
 struct Variant {
   int nt, nv;
-  RowKernel bf16[2], f32[2];  // whole aligned vectors, ragged
+  RowKernel bf16[2], f32;  // bf16: whole aligned vectors, ragged
 };
 
-#define GRPO_VARIANT(NT, NV)                                                                       \
-  {                                                                                                \
-    NT, NV, {k_rows_resident<uint16_t, NT, NV, false>, k_rows_resident<uint16_t, NT, NV, true>},   \
-        {k_rows_resident<float, NT, NV, false>, k_rows_resident<float, NT, NV, true>}              \
+#define GRPO_VARIANT(NT, NV)                                                                     \
+  {                                                                                              \
+    NT, NV, {k_rows_resident<uint16_t, NT, NV, false>, k_rows_resident<uint16_t, NT, NV, true>}, \
+        k_rows_resident<float, NT, NV, false>                                                    \
   }
 
 // Searched in order; the first that holds the row is used.  Rows of 3,073 to 4,096 vectors (a bf16 vocabulary of
@@ -541,6 +769,15 @@ static const RowKernel kPipe[][2] = {
 };  // from 15 vectors on, 14 in registers and the rest in LDS, except 19 (V = 151,936): 13 and 6, 0.3% faster
    // than 15 and 4 and 0.4% faster than 14 and 5, with 12 and 7 or 11 and 8 within 0.1% of it (before the LDS
    // part kept its terms, 15 and 4 was 0.4% faster than 14 and 5)
+// The streaming kernel: 9 LDS vectors and 12 in registers, whole aligned vectors or ragged.  Loss and dlogits in two
+// passes / here: bf16 10,000 x 262,144 2.72 / 1.89 ms (5.6 TB/s of the row read and written once), 12,000 x 200,000
+// 2.56 / 1.80.  13 + 5 and 14 + 6 register vectors, which spill, are 1 to 3% slower, a first read past the caches 11%.
+static const RowKernel kStreamRows[2] = {k_rows_stream<uint16_t, 9, 12, 4, false>,
+                                         k_rows_stream<uint16_t, 9, 12, 4, true>};
+// Rows of up to 4 MiB, beyond which the second read misses more and more (fp32 rows of 4 MB gained 6%).
+constexpr int64_t kStreamMaxRow = (int64_t)1 << 22;
+// k_rows_twice: rows addressed with 32-bit offsets.
+constexpr int64_t kTwiceMaxRow = (int64_t)1 << 30;
 constexpr int kPipeMinNV = 7, kPipeMaxNV = 23;  // at most 15 register vectors and 9 LDS vectors per thread
 constexpr int64_t kPipeMaxT = (int64_t)1 << 30;  // t + (gridDim.x - 1) * chunk + 1 stays far below 2^31
 
@@ -549,17 +786,27 @@ struct Launch {
   int nt;
   unsigned grid;
   int chunk = 1, r0 = 0, chunk2 = 1;
+  unsigned lds = 0;  // dynamic LDS bytes
 };
 
 static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, const void* logits,
                               const void* dlogits, hipStream_t s) {
   const int epv = (dt == GRPO_BF16) ? 8 : 4;
-  const RowForm form = row_form(logits, dlogits, V, ld, 16 / epv);
+  // fp32 rows that are not whole aligned vectors keep the element kernel's column classes: the vector kernels' other
+  // order of fp32 sums, no less exact, moves the small dlogits of a near-certain token by more (to 5e-4 of the root mean
+  // square) than callers that compare in 32 bits allow
+  RowForm form = row_form(logits, dlogits, V, ld, 16 / epv);
+  if (dt == GRPO_F32 && form == RowForm::kRagged) form = RowForm::kElements;
   const int rag = form == RowForm::kRagged;
   if (form != RowForm::kElements) {
     const int64_t nvec = V / epv;  // the most a row has
     const int64_t nv = (nvec + 1023) / 1024;
-    if (dt == GRPO_BF16 && nv >= kPipeMinNV && nv <= kPipeMaxNV && T <= kPipeMaxT) {
+    RowKernel k = nullptr;
+    if (T <= kPipeMaxT) {
+      if (dt == GRPO_BF16 && nv >= kPipeMinNV && nv <= kPipeMaxNV) k = kPipe[nv - kPipeMinNV][rag];
+      else if (dt == GRPO_BF16 && nv > kPipeMaxNV && nvec * 16 <= kStreamMaxRow) k = kStreamRows[rag];
+    }
+    if (k) {
       int n_cu = stream_cu_count(s);  // of the stream's device
       if (n_cu < 1) n_cu = 256;
       // chunks of up to 8 rows (1.6-2.5% faster than single rows at 120,000 x 151,936), but at least four chunks
@@ -571,14 +818,19 @@ static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, c
       // 469 rows instead of 472
       const int64_t r0 = T / (chunk * g) * (chunk * g);
       const int64_t chunk2 = std::max<int64_t>(1, (T - r0 + g - 1) / g);
-      return Launch{kPipe[nv - kPipeMinNV][rag], 1024, (unsigned)g, (int)chunk, (int)r0, (int)chunk2};
+      return Launch{k, 1024, (unsigned)g, (int)chunk, (int)r0, (int)chunk2};
     }
     for (const Variant& v : kVariants) {
-      if ((int64_t)v.nt * v.nv >= nvec) return Launch{dt == GRPO_BF16 ? v.bf16[rag] : v.f32[rag], v.nt, (unsigned)T};
+      if ((int64_t)v.nt * v.nv >= nvec) return Launch{dt == GRPO_BF16 ? v.bf16[rag] : v.f32, v.nt, (unsigned)T};
     }
     return Launch{nullptr, 0, 0};  // two passes
   }
-  return Launch{dt == GRPO_BF16 ? k_rows_generic<uint16_t> : k_rows_generic<float>, 256, (unsigned)T};
+  // staged in LDS where two workgroups fit a CU: alone on its CU, 256 threads took 0.96 ms at fp32 10,000 x 32,003
+  // against 0.80 with every sweep from memory
+  const int64_t bytes = V * (16 / epv);
+  const bool staged = bytes <= 79 * 1024;
+  return Launch{dt == GRPO_BF16 ? k_rows_elements<uint16_t> : k_rows_elements<float>, 256, (unsigned)T, staged, 0, 1,
+                staged ? (unsigned)bytes : 0u};
 }
 
 }  // namespace grpo
@@ -633,8 +885,10 @@ extern "C" int grpo_loss_fwd_bwd(const void* logits, int32_t dtype, int64_t T, i
     const bool timed = aux && aux->hot_begin && aux->hot_end;
     if (timed && hipEventRecord(aux->hot_begin, s) != hipSuccess) return GRPO_ERR_HIP;
     if (k.k) {
-      hipLaunchKernelGGL(k.k, dim3(k.grid), dim3(k.nt), 0, s, a);
+      hipLaunchKernelGGL(k.k, dim3(k.grid), dim3(k.nt), k.lds, s, a);
       if (hipGetLastError() != hipSuccess) return GRPO_ERR_HIP;
+    } else if (dt == GRPO_F32 && V * 4 <= kTwiceMaxRow) {
+      if (launch_rows_twice(logits, dlogits, T, ld, a.tok, s) != hipSuccess) return GRPO_ERR_HIP;
     } else {
       // the whole vocabulary as one shard: its records, then the merge (trivial), epilogue and dlogits
       grpo_vocab_stats* rec = reinterpret_cast<grpo_vocab_stats*>(w + L.records);

@@ -48,11 +48,13 @@ def _loss(cfg, st, lg, act, behave, adv, V, dl, gs):
 
 
 # bf16: below a vector, the resident variants' ends (64 x 1 and 256 x 4 vectors and one more), the persistent kernel's
-# first and last sizes and one between two of its vector counts, a padded head, past it (two passes); fp32 the same
+# first and last sizes and one between two of its vector counts, a padded head, past it (the streaming kernel); fp32
+# rows, in the loss element by element, staged in LDS (up to 20,224 elements) or not; bf16 beyond 4 MiB (two passes)
 SIZES = [(1, 1, "bf16"), (7, 7, "bf16"), (8, 9, "bf16"), (519, 519, "bf16"), (8199, 8201, "bf16"), (32003, 32003, "bf16"),
          (49159, 49159, "bf16"), (49161, 49162, "bf16"), (57353, 57353, "bf16"), (151669, 151936, "bf16"),
          (188423, 188423, "bf16"), (188431, 188431, "bf16"), (3, 3, "f32"), (259, 261, "f32"), (4093, 4093, "f32"),
-         (77825, 77825, "f32"), (77831, 77832, "f32"), (151669, 151936, "f32")]
+         (77825, 77825, "f32"), (77831, 77832, "f32"), (20223, 20223, "f32"), (20225, 20225, "f32"),
+         (151669, 151936, "f32"), (2097159, 2097159, "bf16"), (2097161, 2097161, "bf16")]
 
 
 @pytest.mark.parametrize("offset", [0, 1])
@@ -79,10 +81,12 @@ def test_loss_rows(V, ld, dtype, offset):
         assert (dl[:, V:] == 7.0).all()  # columns past V are left alone
 
 
-def test_persistent_kernel_many_ragged_rows():
-    # several rows per workgroup, edges and vector counts changing from row to row, dlogits over the logits
-    V, T = 57353, 1200
-    cfg, st, lg, act, behave, adv = _batch(V, V, "bf16", 3, T=T, seed=8)
+@pytest.mark.parametrize("V,T,dtype", [(57353, 1200, "bf16"), (188435, 600, "bf16"), (188440, 600, "bf16"),
+                                       (77832, 600, "f32"), (77831, 300, "f32")])
+def test_dlogits_over_the_logits(V, T, dtype):
+    # bf16: several rows per workgroup, edges and vector counts changing from row to row; fp32: the kernel that reads a
+    # row twice, and element by element; dlogits over the logits
+    cfg, st, lg, act, behave, adv = _batch(V, V, dtype, 0 if V % 8 == 0 else 3, T=T, seed=8)
     before = lg.clone()
     seg = oracle.segments(st.T, st.step_tok_off, st.traj_step_off)
     ref = oracle.loss_rows(to_np_logits(before), act.cpu().numpy(), behave.cpu().numpy(), None,
@@ -92,7 +96,7 @@ def test_persistent_kernel_many_ragged_rows():
     assert abs(loss - ref.loss) <= LOSS_RTOL * np.abs(ref.token_contrib).sum()
     r = ref.dlogits * gs
     err = np.abs(dl_to_f64(lg) - r)
-    assert (err <= 2.0 ** -8 * np.abs(r) + 1e-5 * np.abs(r).max(axis=1, keepdims=True)).all()
+    assert (err <= (2.0 ** -8 if dtype == "bf16" else 0.0) * np.abs(r) + 1e-5 * np.abs(r).max(axis=1, keepdims=True)).all()
 
 
 @pytest.mark.parametrize("offset", [0, 1])

@@ -27,6 +27,8 @@ def scan_scalar_reads(asm: str) -> list:
             if fn2 != fn or waited >= WAIT_STATES:
                 break
             op = s2.split()[0]
+            if op == "s_branch":
+                break  # what stands before it does not fall through to the load
             if op.startswith(("v_readfirstlane", "v_readlane")) and int(re.search(r"\bs(\d+)\b", s2).group(1)) in reads:
                 hits.append((fn, s2, s))
             waited += int(s2.split()[1]) + 1 if op == "s_nop" else 1
