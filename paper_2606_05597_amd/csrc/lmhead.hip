@@ -151,14 +151,16 @@ __global__ __launch_bounds__(LmCfg::NT) void k_lm_partial(const PartialArgs p) {
   lm_partial_epilogue<false, TERMS>(p, acc, m0, n0, tn, sm);
 }
 
-// The forward-only fused product: tile partials with the entropy moment, no logits stored.
-__global__ __launch_bounds__(LmCfg::NT) void k_lm_partial_ent(const PartialArgs p) {
+// The forward-only fused product: tile partials with the entropy moment (ENT), no logits stored.
+template <bool ENT, bool PACKED>
+__global__ __launch_bounds__(LmCfg::NT) void k_lm_partial_fwd(const PartialArgs p) {
   __shared__ __attribute__((aligned(16))) GemmSmem sm;
   int tm, tn;
   if (!gemm_tile_of(blockIdx.x, gridDim.x, tiles_of(p.g.M), tiles_of(p.g.N), tm, tn)) return;
   g_f32x16 acc[LmCfg::IB][LmCfg::JB];
-  gemm_mainloop<LmCfg>(p.g, tm * TILE, tn * TILE, acc, sm.s);
-  lm_partial_epilogue<true, false>(p, acc, tm * TILE, tn * TILE, tn, sm);
+  if constexpr (PACKED) gemm_mainloop_packed<LmCfg>(p.g, tm * TILE, tn * TILE, acc, sm.s);
+  else gemm_mainloop<LmCfg>(p.g, tm * TILE, tn * TILE, acc, sm.s);
+  lm_partial_epilogue<ENT, false>(p, acc, tm * TILE, tn * TILE, tn, sm);
 }
 
 template <bool ENT, bool TERMS>
@@ -429,6 +431,7 @@ struct LmLogpArgs {
 
 __global__ void k_lm_clear_flags(int32_t* f) { *f = 0; }
 
+template <bool PACKED>
 __global__ __launch_bounds__(256) void k_lm_logp(const LmLogpArgs a) {
   __shared__ RowStatsSmem sh;
   __shared__ double sh_t[4];
@@ -438,7 +441,7 @@ __global__ __launch_bounds__(256) void k_lm_logp(const LmLogpArgs a) {
   float M;
   double S, za;
   const float2* pr = a.part + (int64_t)t * a.n_tiles;
-  lm_row_stats(pr, a.n_tiles, a.h + (int64_t)t * a.H, a.WT, ok ? act : -1, a.H, sh, M, S, za);
+  lm_row_stats<PACKED>(pr, a.n_tiles, a.h + (int64_t)t * a.H, a.WT, ok ? act : -1, a.H, sh, M, S, za);
   double Tm = 0.0;
   if (a.entropy) {
     // the row's second moment about M: sum over tiles of e^(m_j - M) (T_j + S_j (m_j - M))
@@ -493,12 +496,18 @@ __global__ __launch_bounds__(256) void k_lm_shard_scale(const ShardScaleArgs a) 
   a.rs[t] = rs;
 }
 
+// Rows 8 t8 .. 8 t8 + 7 of column `col` of D, one lane's 16 bytes of D^T in the fragment-packed layout (N = columns,
+// K = `rows` rows of D, a multiple of 64).
+__device__ __forceinline__ uint16_t* dt_packed(uint16_t* DT, int64_t col, int t8, int rows) {
+  return DT + ((col >> 5) * (rows >> 4) + (t8 >> 1)) * 512 + ((t8 & 1) * 32 + (col & 31)) * 8;
+}
+
 // ---- pass 2a: recompute z_c, form D_c = g (softmax - onehot), store D_c and D_c^T --
 struct DlogitsArgs {
   GemmArgs g;            // A = h [T, H] (M = Tp), B = W^T rows of the chunk [Cw, H]
   const RowScale* rs;    // [Tp]
   uint16_t* D;           // the chunk's columns of the pair buffer, row stride C
-  uint16_t* DT;          // [chunk width, Tp]
+  uint16_t* DT;          // D^T [chunk width, Tp] in the fragment-packed layout
   int c0, C, Tp;         // C: D's row stride (twice the chunk when chunks are paired)
 };
 
@@ -570,8 +579,8 @@ __global__ __launch_bounds__(LmCfg::NT) void k_lm_dlogits(const DlogitsArgs p) {
     for (int it = 0; it < 8; ++it) {  // D^T: 8 columns per pass, 8 lanes per 64-row column
       const int lc = it * 8 + (lane >> 3), rc = lane & 7;
       const u32x4 v = *reinterpret_cast<const u32x4*>(stT + lc * 64 + dt_chunk(lc, rc) * 8);
-      const int64_t col = n0 + wn * LmCfg::WTN + lc;
-      *reinterpret_cast<u32x4*>(p.DT + col * p.Tp + m0 + wm * LmCfg::WTM + half * 64 + rc * 8) = v;
+      const int col = n0 + wn * LmCfg::WTN + lc, t8 = (m0 + wm * LmCfg::WTM + half * 64) / 8 + rc;
+      *reinterpret_cast<u32x4*>(dt_packed(p.DT, col, t8, p.Tp)) = v;
     }
   }
 }
@@ -663,7 +672,7 @@ __device__ __forceinline__ void lm_dh_tile(DhArgs p, int bid, int nblocks, GemmS
 
 // ---- pass 2c: dW[:, chunks] = h^T D -------------------------------------------------
 struct DwArgs {
-  GemmArgs g;     // A = h^T [H, Tp], B = D^T of the pair [width, Tp], K = Tp (with PACKED: D^T packed)
+  GemmArgs g;     // A = h^T [H, Tp], B = D^T of the pair [width, Tp] packed, K = Tp
   float* dw;      // [H, V]
   int64_t V;
   int c0, accumulate;
@@ -674,7 +683,7 @@ struct DwArgs {
 // panels shared along M).  With K = a token block, h^T is small ([H, 8192]: 59 MB, held by the last-level cache)
 // and D^T is the whole vocabulary, so N_MAJOR reads D^T from HBM once instead of once per 8 of H's 14 tiles
 // (3-4% faster on the bare product, 0.3% on the whole blocked call); with K = the whole batch h^T is the large operand and the first order is kept.
-template <bool N_MAJOR, bool PACKED = false>
+template <bool N_MAJOR>
 __device__ __forceinline__ void lm_dw_tile(const DwArgs& p, int bid, int nblocks, GemmSmem& sm) {
   int tm, tn;
   if (N_MAJOR) {
@@ -686,8 +695,7 @@ __device__ __forceinline__ void lm_dw_tile(const DwArgs& p, int bid, int nblocks
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / LmCfg::WGN, wn = wave % LmCfg::WGN;
   g_f32x16 acc[LmCfg::IB][LmCfg::JB];
-  if constexpr (PACKED) gemm_mainloop_packed<LmCfg>(p.g, m0, n0, acc, sm.s);
-  else gemm_mainloop<LmCfg>(p.g, m0, n0, acc, sm.s);
+  gemm_mainloop_packed<LmCfg>(p.g, m0, n0, acc, sm.s);
   // Per 32-row block i: with accumulate, all of its old values are loaded first and waited for once, then
   // added and stored (element by element, every load would wait for the memory in turn).
   auto store = [&](auto full, auto accumulate) {
@@ -729,48 +737,42 @@ __device__ __forceinline__ void lm_dw_tile(const DwArgs& p, int bid, int nblocks
   }
 }
 
-// Both backward products of a pair of chunks in one launch.  A dW tile runs over K = Tp, four to eight times
-// longer than a dhidden tile (K = the pair's width), and a chunk's dW alone has 1.75 tiles per CU at the
-// benchmark's shape; launched first, the long dW tiles are followed on every CU by short dhidden tiles, which
-// fill the round the dW tiles leave ragged.
-struct DhDwArgs {
+// Both backward products in one launch, the longer tiles first: dispatched first, they spread over the CUs, and the
+// short ones fill the time the last of them leave (at 65,536 rows a chunk's dW alone has 1.75 tiles per CU).  A dW tile
+// runs over K = the rows, a dhidden tile over K = the columns (a pair of chunks, a shard, the whole vocabulary).
+// PACKED_W: W comes in the fragment-packed layout, as D^T always does (4% faster on a dW tile than staged through LDS).
+struct BackwardArgs {
   DhArgs dh;
   DwArgs dw;
-  int dw_blocks;  // blocks [0, dw_blocks) take dW tiles, the rest dhidden tiles; a multiple of 8
+  int first;  // blocks [0, first) take the tiles that go first; a multiple of 8
 };
 
-__global__ __launch_bounds__(LmCfg::NT) void k_lm_dh_dw(const DhDwArgs p) {
+template <bool DH_FIRST, bool PACKED_W>
+__global__ __launch_bounds__(LmCfg::NT) void k_lm_backward(const BackwardArgs p) {
   __shared__ __attribute__((aligned(16))) GemmSmem sm;
-  const int b = blockIdx.x;
-  if (b < p.dw_blocks) lm_dw_tile<false>(p.dw, b, p.dw_blocks, sm);
-  else lm_dh_tile(p.dh, b - p.dw_blocks, (int)gridDim.x - p.dw_blocks, sm);
+  const int b = blockIdx.x, rest = (int)gridDim.x - p.first;
+  if (DH_FIRST) {
+    if (b < p.first) lm_dh_tile<PACKED_W>(p.dh, b, p.first, sm);
+    else lm_dw_tile<true>(p.dw, b - p.first, rest, sm);
+  } else {
+    if (b < p.first) lm_dw_tile<false>(p.dw, b, p.first, sm);
+    else lm_dh_tile<PACKED_W>(p.dh, b - p.first, rest, sm);
+  }
 }
 
-// The token-blocked schedule's backward launch: the dhidden tiles (K = the whole vocabulary) first, then the dW
-// tiles (K = the block's rows).  A dhidden tile is then the longest unit by far; dispatched first, the long tiles
-// spread over the CUs and the many short dW tiles fill the time the last of them leave.  D^T comes in the
-// fragment-packed layout, W too when PACKED_W (dh_plan says when it doesn't).
-struct DhThenDwArgs {
-  DhArgs dh;
-  DwArgs dw;
-  int dh_blocks;  // blocks [0, dh_blocks) take dhidden tiles, the rest dW tiles; a multiple of 8
-};
-
-template <bool PACKED_W>
-__global__ __launch_bounds__(LmCfg::NT) void k_lm_dh_then_dw(const DhThenDwArgs p) {
-  __shared__ __attribute__((aligned(16))) GemmSmem sm;
-  const int b = blockIdx.x;
-  if (b < p.dh_blocks) lm_dh_tile<PACKED_W>(p.dh, b, p.dh_blocks, sm);
-  else lm_dw_tile<true, true>(p.dw, b - p.dh_blocks, (int)gridDim.x - p.dh_blocks, sm);
+// dhidden = the sum of the K ranges' fp32 partials [splits][n], in range order, rounded to bf16 or kept; n a multiple
+// of 4.
+__device__ __forceinline__ void store4(uint16_t* p, f32x4 v) {
+  *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
 }
-
-// dhidden = the sum of the K ranges' fp32 partials [splits][n], in range order, rounded to bf16; n a multiple of 4.
+__device__ __forceinline__ void store4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
+template <typename Tout>
 __global__ __launch_bounds__(256) void k_lm_dh_sum(const float* __restrict__ part, int splits, int64_t n,
-                                                   uint16_t* __restrict__ dh) {
+                                                   Tout* __restrict__ dh) {
   for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < n; i += (int64_t)gridDim.x * 1024) {
     f32x4 s = *reinterpret_cast<const f32x4*>(part + i);
     for (int q = 1; q < splits; ++q) s += *reinterpret_cast<const f32x4*>(part + (int64_t)q * n + i);
-    *reinterpret_cast<u32x2*>(dh + i) = u32x2{pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3])};
+    store4(dh + i, s);
   }
 }
 
@@ -783,10 +785,9 @@ struct BlockDArgs {
   int n_tiles;
   const RowScale* rs;  // [rows] the block's row scales
   uint16_t* D;         // [rows, ld]
-  uint16_t* DT;        // [ld, rows], or with packed_dt D^T in the fragment-packed layout (N = ld, K = rows)
+  uint16_t* DT;        // D^T in the fragment-packed layout (N = ld, K = rows)
   int64_t ld;          // a multiple of 64; columns V..ld get D = 0
   int V, rows;         // rows: a multiple of 64
-  int packed_dt;
 };
 constexpr int kBlockDStrip = 512;  // columns per work item: eight 64 x 64 tiles
 constexpr int64_t kBlockDMaxGrid = 1 << 20;  // workgroups per launch at most; they loop over the rest
@@ -804,8 +805,7 @@ static unsigned block_d_grid(int64_t rows, int64_t ld, int grid) {
 // 2 x 4 pieces (rows 2p, 2p + 1 of four columns, p = tid / 16 and p + 16): two 16-byte logit loads each; the D
 // rows go out as 8-byte stores (16 lanes fill a 128-byte line); for D^T every column's row pair is packed into
 // one 32-bit LDS word (stride 33 words per column), read back as four words = eight rows, and stored 16 bytes
-// at a time (8 lanes per 128-byte column piece, or with packed_dt one packed lane's 16 bytes, 8 lanes of
-// consecutive columns side by side).  Two LDS buffers, one barrier per tile.
+// at a time (one packed lane's 16 bytes, 8 lanes of consecutive columns side by side).  Two LDS buffers, one barrier per tile.
 __global__ __launch_bounds__(256) void k_lm_block_d(const BlockDArgs a) {
   constexpr int kLdw = 33;
   __shared__ uint32_t tu[2][64 * kLdw];
@@ -861,9 +861,7 @@ __global__ __launch_bounds__(256) void k_lm_block_d(const BlockDArgs a) {
         const u32x4 v = {src[0], src[1], src[2], src[3]};
         const int64_t vc = cs + it * 64 + col;
         const int t8 = (r0 >> 3) + rc;  // rows 8 t8 .. 8 t8 + 7 of column vc: one packed lane's 16 bytes
-        uint16_t* dst = a.packed_dt ? a.DT + ((vc >> 5) * (a.rows >> 4) + (t8 >> 1)) * 512 + ((t8 & 1) * 32 + (vc & 31)) * 8
-                                    : a.DT + vc * a.rows + 8 * t8;
-        *reinterpret_cast<u32x4*>(dst) = v;
+        *reinterpret_cast<u32x4*>(dt_packed(a.DT, vc, t8, a.rows)) = v;
       }
     }
   }
@@ -932,8 +930,7 @@ __global__ __launch_bounds__(256) void k_lm_block_d16(const BlockDArgs a) {
         const u32x4 v = {src[0], src[1], src[2], src[3]};
         const int64_t vc = cs + it * 64 + col;
         const int t8 = (r0 >> 3) + rc;  // rows 8 t8 .. 8 t8 + 7 of column vc: one packed lane's 16 bytes
-        uint16_t* dst = a.DT + ((vc >> 5) * (a.rows >> 4) + (t8 >> 1)) * 512 + ((t8 & 1) * 32 + (vc & 31)) * 8;
-        *reinterpret_cast<u32x4*>(dst) = v;
+        *reinterpret_cast<u32x4*>(dt_packed(a.DT, vc, t8, a.rows)) = v;
       }
     }
   }
@@ -1070,6 +1067,13 @@ static void lm_transpose(const uint16_t* W16, const uint16_t* h16, int64_t T, in
                        s, h16, H, (int)T, (int)H, hT, (int64_t)Tp, Tp);
 }
 
+// W^T from W [H, V], as the matrix [V, H] or in the fragment-packed layout (N = V, K = H).
+static void lm_wt(const uint16_t* W16, int64_t H, int64_t V, bool packed, uint16_t* WT, hipStream_t s) {
+  const dim3 grid((unsigned)((V + 63) / 64), (unsigned)((H + 63) / 64));
+  if (packed) hipLaunchKernelGGL(k_pack_t, grid, dim3(256), 0, s, W16, V, (int)H, (int)V, WT);
+  else hipLaunchKernelGGL(k_transpose_bf16, grid, dim3(256), 0, s, W16, V, (int)H, (int)V, WT, H, (int)H);
+}
+
 static void lm_pass1(const uint16_t* h16, const uint16_t* WT, int64_t T, int64_t H, int64_t V, float2* part,
                      int n_tiles, hipStream_t s) {
   PartialArgs pa{};
@@ -1096,6 +1100,16 @@ struct Pass2 {
   int Tp, C, accumulate_dw;
 };
 
+// The two products' launch, the dhidden tiles first or the dW tiles.
+static void launch_backward(BackwardArgs& ba, unsigned dh_blocks, unsigned dw_blocks, bool dh_first, bool packed_w,
+                            hipStream_t s) {
+  ba.first = (int)(dh_first ? dh_blocks : dw_blocks);
+  const dim3 grid(dh_blocks + dw_blocks), nt(LmCfg::NT);
+  if (packed_w) hipLaunchKernelGGL((k_lm_backward<true, true>), grid, nt, 0, s, ba);
+  else if (dh_first) hipLaunchKernelGGL((k_lm_backward<true, false>), grid, nt, 0, s, ba);
+  else hipLaunchKernelGGL((k_lm_backward<false, false>), grid, nt, 0, s, ba);
+}
+
 static void lm_pass2(const Pass2& q, hipStream_t s) {
   // the backward products take the chunks in pairs (D holds two side by side, D^T one above the other), which
   // halves the passes over dhidden's fp32 accumulator and gives one dW launch per pair
@@ -1117,7 +1131,7 @@ static void lm_pass2(const Pass2& q, hipStream_t s) {
     if ((c & 1) || c == n_chunks - 1) {
       const int p0 = c & ~1;                  // first chunk of the pair
       const int width = (c & 1) ? C + Cw : Cw;  // the pair's vocabulary columns
-      DhDwArgs ba;
+      BackwardArgs ba;
       ba.dh.g = GemmArgs{q.D, q.W16 + (int64_t)p0 * C, ldD, q.V, (int)q.T, (int)q.H, width};
       ba.dh.acc = q.acc;
       ba.dh.dh = q.dh16;
@@ -1128,8 +1142,9 @@ static void lm_pass2(const Pass2& q, hipStream_t s) {
       ba.dw.V = q.V;
       ba.dw.c0 = p0 * C;
       ba.dw.accumulate = q.accumulate_dw;
-      ba.dw_blocks = (int)gemm_grid(q.H, width).x;
-      hipLaunchKernelGGL(k_lm_dh_dw, dim3((unsigned)ba.dw_blocks + gemm_grid(q.T, q.H).x), dim3(LmCfg::NT), 0, s, ba);
+      // the longer tiles first: at 700, 4,096 and 8,192 rows of 3,584 x 151,936 (dhidden tiles longer) the whole call
+      // took 7.29, 16.5 and 31.7 ms with the dW tiles first and takes 6.85, 16.0 and 30.6
+      launch_backward(ba, gemm_grid(q.T, q.H).x, gemm_grid(q.H, width).x, width > q.Tp, false, s);
     }
   }
 }
@@ -1405,7 +1420,7 @@ extern "C" int fused_lmhead_grpo_blocked(const void* hidden, const void* w_lm, i
   auto dpass = [&](int b, hipStream_t st, int grid) {
     const int rows_p = rows64(rows_of(b));
     const BlockDArgs da{nullptr, e_of(b), part_of(b), L.n_tiles, rs + (int64_t)b * L.Tbp, D, DT, L.ldz, (int)V,
-                        rows_p, 1};
+                        rows_p};
     hipLaunchKernelGGL(k_lm_block_d16, dim3(block_d_grid(rows_p, L.ldz, grid)), dim3(256), 0, st, da);
   };
   // block b's dhidden rows = D W^T (K = V) and dW (+)= h^T D (K = the block's rows, zero-padded), on s
@@ -1416,7 +1431,7 @@ extern "C" int fused_lmhead_grpo_blocked(const void* hidden, const void* w_lm, i
     // the partials of a split go where the block's terms were, which its D pass has read
     const DhPlan plan = dh_plan(rows, H, V, acc_dw, L.Tbp * L.ldz / 2, n_cu);
     const bool packed = pack_w && plan.splits == 1;
-    DhThenDwArgs ba;
+    BackwardArgs ba;
     ba.dh.g = packed ? GemmArgs{D, WP, L.ldz, 0, rows, (int)H, (int)V} : GemmArgs{D, W16, L.ldz, V, rows, (int)H, (int)V};
     ba.dh.acc = reinterpret_cast<float*>(e_of(b));
     ba.dh.dh = dh16 + t0 * H;
@@ -1429,14 +1444,11 @@ extern "C" int fused_lmhead_grpo_blocked(const void* hidden, const void* w_lm, i
     ba.dw.V = V;
     ba.dw.c0 = 0;
     ba.dw.accumulate = acc_dw;
-    ba.dh_blocks = (int)gemm_grid(rows, H, plan.splits).x;
-    const dim3 grid((unsigned)ba.dh_blocks + gemm_grid(H, V).x);
-    if (packed) hipLaunchKernelGGL(k_lm_dh_then_dw<true>, grid, dim3(LmCfg::NT), 0, s, ba);
-    else hipLaunchKernelGGL(k_lm_dh_then_dw<false>, grid, dim3(LmCfg::NT), 0, s, ba);
+    launch_backward(ba, gemm_grid(rows, H, plan.splits).x, gemm_grid(H, V).x, true, packed, s);
     if (plan.splits > 1) {
       const int64_t n = (int64_t)rows * H;
-      hipLaunchKernelGGL(k_lm_dh_sum, dim3((unsigned)std::min<int64_t>((n + 1023) / 1024, 4096)), dim3(256), 0, s,
-                         ba.dh.acc, plan.splits, n, ba.dh.dh);
+      hipLaunchKernelGGL(k_lm_dh_sum<uint16_t>, dim3((unsigned)std::min<int64_t>((n + 1023) / 1024, 4096)), dim3(256), 0,
+                         s, ba.dh.acc, plan.splits, n, ba.dh.dh);
     }
   };
   const bool two = s_aux && s_aux != s && n_blocks > 1;
@@ -1528,22 +1540,28 @@ extern "C" int fused_lmhead_token_logp(const void* hidden, const void* w_lm, int
   float2* part = reinterpret_cast<float2*>(w + L.part);
   float* part_t = reinterpret_cast<float*>(w + L.part_t);
   const int n_tiles = (int)((V + TILE - 1) / TILE);
-  lm_transpose(static_cast<const uint16_t*>(w_lm), h16, T, H, V, 0, WT, nullptr, s);
-  if (token_entropy) {
-    PartialArgs pa{};
-    pa.g = GemmArgs{h16, WT, H, H, (int)T, (int)V, (int)H};
-    pa.part = part;
-    pa.n_tiles = n_tiles;
-    pa.z = nullptr;
-    pa.ldz = 0;
-    pa.part_t = part_t;
-    hipLaunchKernelGGL(k_lm_partial_ent, gemm_grid(T, V), dim3(LmCfg::NT), 0, s, pa);
-  } else {
-    lm_pass1(h16, WT, T, H, V, part, n_tiles, s);
-  }
+  // W^T packed where its 32-column blocks are whole, so that it takes no more room than as a matrix, and K is long:
+  // matrix / packed, 4,001 x 3,584 x 151,936 4.21 / 4.09 ms, 12,000 rows 11.92 / 11.49, 4,001 x 1,024 x 32,000 0.328 /
+  // 0.331
+  const bool packed = V % 32 == 0 && H >= 2048;
+  lm_wt(static_cast<const uint16_t*>(w_lm), H, V, packed, WT, s);
+  PartialArgs pa{};
+  pa.g = GemmArgs{h16, WT, H, H, (int)T, (int)V, (int)H};
+  pa.part = part;
+  pa.n_tiles = n_tiles;
+  pa.part_t = part_t;
   const LmLogpArgs la{part, token_entropy ? part_t : nullptr, h16, WT, actions, token_logp, token_entropy,
                       error_flags, V, (int)T, (int)H, n_tiles};
-  hipLaunchKernelGGL(k_lm_logp, dim3((unsigned)T), dim3(256), 0, s, la);
+  const dim3 grid = gemm_grid(T, V), nt(LmCfg::NT), rows((unsigned)T);
+  if (packed) {
+    if (token_entropy) hipLaunchKernelGGL((k_lm_partial_fwd<true, true>), grid, nt, 0, s, pa);
+    else hipLaunchKernelGGL((k_lm_partial_fwd<false, true>), grid, nt, 0, s, pa);
+    hipLaunchKernelGGL(k_lm_logp<true>, rows, dim3(256), 0, s, la);
+  } else {
+    if (token_entropy) hipLaunchKernelGGL((k_lm_partial_fwd<true, false>), grid, nt, 0, s, pa);
+    else hipLaunchKernelGGL((k_lm_partial_fwd<false, false>), grid, nt, 0, s, pa);
+    hipLaunchKernelGGL(k_lm_logp<false>, rows, dim3(256), 0, s, la);
+  }
   return hipGetLastError() == hipSuccess ? GRPO_OK : GRPO_ERR_HIP;
 }
 
@@ -1655,21 +1673,38 @@ extern "C" int fused_lmhead_grpo_vocab_shard(const void* hidden, const void* w_s
   if (logits_in) {
     // D, D^T of the whole shard from its stored logits, then dW (K = Tp) and the fp32 partial dhidden (K = V_shard)
     // in one launch, the long dW tiles first
-    const BlockDArgs da{logits_in, nullptr, nullptr, 0, rs, D, DT, Vsp, (int)V_shard, Tp, 0};
+    const BlockDArgs da{logits_in, nullptr, nullptr, 0, rs, D, DT, Vsp, (int)V_shard, Tp};
     hipLaunchKernelGGL(k_lm_block_d, dim3(block_d_grid(Tp, Vsp, 0)), dim3(256), 0, s, da);
-    DhDwArgs ba;
+    // the partials of a split go where W^T would be
+    const int n_cu = stream_cu_count(s);
+    if (n_cu < 1) return GRPO_ERR_HIP;
+    const DhPlan plan = dh_plan(T, H, V_shard, accumulate_dw, V_shard * H / 2, n_cu);
+    BackwardArgs ba;
     ba.dh.g = GemmArgs{D, W16, Vsp, V_shard, (int)T, (int)H, (int)V_shard};
-    ba.dh.acc = dhidden_partial;
+    ba.dh.acc = plan.splits > 1 ? reinterpret_cast<float*>(WT) : dhidden_partial;
     ba.dh.dh = nullptr;
     ba.dh.first = 1;
     ba.dh.last = 0;
+    ba.dh.splits = plan.splits;
+    ba.dh.split_k = plan.split_k;
     ba.dw.g = GemmArgs{hT, DT, Tp, Tp, (int)H, (int)V_shard, Tp};
     ba.dw.dw = dw_shard;
     ba.dw.V = V_shard;
     ba.dw.c0 = 0;
     ba.dw.accumulate = accumulate_dw;
-    ba.dw_blocks = (int)gemm_grid(H, V_shard).x;
-    hipLaunchKernelGGL(k_lm_dh_dw, dim3((unsigned)ba.dw_blocks + gemm_grid(T, H).x), dim3(LmCfg::NT), 0, s, ba);
+    // The dhidden tiles first where they leave more than a tenth of the launch idle in their last round (the dW tiles
+    // then fill it), else the dW tiles.  At 3,584 x 18,992, dhidden / dW first: 5,000 rows 2.14 / 2.55 ms, 8,192 3.39 /
+    // 3.32, 12,000 4.94 / 4.89.
+    const unsigned dh_blocks = gemm_grid(T, H, plan.splits).x, dw_blocks = gemm_grid(H, V_shard).x;
+    const int64_t rounds = (dh_blocks + n_cu - 1) / n_cu, idle = (rounds * n_cu - dh_blocks) * V_shard;
+    const int64_t all = (int64_t)dh_blocks * V_shard + (int64_t)dw_blocks * Tp;
+    const bool dh_first = plan.splits > 1 || (V_shard > Tp && 10 * idle > all);
+    launch_backward(ba, dh_blocks, dw_blocks, dh_first, false, s);
+    if (plan.splits > 1) {
+      const int64_t n = T * H;
+      hipLaunchKernelGGL(k_lm_dh_sum<float>, dim3((unsigned)std::min<int64_t>((n + 1023) / 1024, 4096)), dim3(256), 0, s,
+                         ba.dh.acc, plan.splits, n, dhidden_partial);
+    }
   } else {
     lm_pass2(Pass2{h16, W16, WT, hT, rs, D, DT, dhidden_partial, nullptr, dw_shard, T, H, V_shard, Tp, vocab_chunk,
                    accumulate_dw},
