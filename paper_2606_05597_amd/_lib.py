@@ -107,6 +107,9 @@ def load() -> ctypes.CDLL:
         lib.fused_lmhead_vocab_shard_logits_bytes.argtypes = [I64, I64]
         lib.fused_lmhead_vocab_shard_logits_bytes.restype = SZ
         lib.fused_lmhead_grpo_vocab_shard.restype = ctypes.c_int
+        # the binding's own (autograd.py), not declared in grpo.h
+        lib.grpo_binding_scale_to_bf16.argtypes = [P, P, P, I64, P]
+        lib.grpo_binding_scale_to_bf16.restype = ctypes.c_int
         lib.grpo_status_str.argtypes = [ctypes.c_int]
         lib.grpo_status_str.restype = ctypes.c_char_p
         _lib = lib

@@ -17,7 +17,7 @@ from __future__ import annotations
 
 import torch
 
-from . import fused_lmhead_grpo, fused_lmhead_grpo_blocked, grpo_loss_fwd_bwd
+from . import _check, _lib, _ptr, _stream, fused_lmhead_grpo, fused_lmhead_grpo_blocked, grpo_loss_fwd_bwd
 
 _UPSTREAM = ("scale", "unit")
 
@@ -33,6 +33,25 @@ def _apply_upstream(mode, grads, grad_output):
     if mode == "unit":
         return grads
     return tuple(None if t is None else torch.mul(t, grad_output.to(t.dtype)) for t in grads)
+
+
+def _plain(t):
+    """A tensor whose memory a kernel may be handed: no subclass, not batched or otherwise wrapped by a transform."""
+    return type(t) is torch.Tensor and not torch._C._functorch.is_functorch_wrapped_tensor(t) and t.is_cuda
+
+
+def _scaled_to_bf16(t, grad_output):
+    """(t * grad_output in fp32) rounded to bf16, in one pass over t where nothing has to see the two operations: no
+    graph of the backward, no transform of it, a plain contiguous t as the library wrote it."""
+    if (torch.is_grad_enabled() or torch.compiler.is_compiling() or not (_plain(t) and _plain(grad_output))
+            or t.dtype != torch.float32 or not t.is_contiguous() or t.data_ptr() % 16 or grad_output.numel() != 1
+            or grad_output.device != t.device):
+        return torch.mul(t, grad_output.to(t.dtype)).to(torch.bfloat16)
+    out = torch.empty_like(t, dtype=torch.bfloat16)
+    g = grad_output.to(torch.float32)
+    _check(_lib.load().grpo_binding_scale_to_bf16(_ptr(t), _ptr(g), _ptr(out), t.numel(), _stream(None)),
+           "grpo_binding_scale_to_bf16")
+    return out
 
 
 class GrpoLoss(torch.autograd.Function):
@@ -80,13 +99,14 @@ class FusedLmHeadGrpoLoss(torch.autograd.Function):
         loss, dhidden, dw = entry(hidden.detach(), w_lm.detach(), actions, behave_logp, adv, step_tok_off,
                                   traj_step_off, group_size, **opts)
         ctx.save_for_backward(dhidden, dw)
-        ctx.w_dtype = w_lm.dtype
         return loss.view(())
 
     @staticmethod
     def backward(ctx, grad_output):
         dhidden, dw = ctx.saved_tensors
-        dhidden, dw = _apply_upstream(ctx.upstream, (dhidden, dw), grad_output)
-        dh = dhidden if ctx.needs_input_grad[0] else None
-        dW = dw.to(ctx.w_dtype) if ctx.needs_input_grad[1] else None
+        dh = dW = None
+        if ctx.needs_input_grad[0]:
+            (dh,) = _apply_upstream(ctx.upstream, (dhidden,), grad_output)
+        if ctx.needs_input_grad[1]:  # w_lm is bf16 (the entry points take nothing else)
+            dW = dw.to(torch.bfloat16) if ctx.upstream == "unit" else _scaled_to_bf16(dw, grad_output)
         return dh, dW, None, None, None, None, None, None, None

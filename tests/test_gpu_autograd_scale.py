@@ -1,0 +1,40 @@
+"""The fused wrapper's dW: the one pass that scales and rounds it against the two torch operations, to the bit, over
+sizes with and without a remainder, special values, and the forms that still go through torch."""
+import math
+
+import pytest
+import torch
+
+from paper_2606_05597_amd.autograd import _scaled_to_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 2047, 2049, 65536 * 2048 + 2048 * 3 + 5])
+@pytest.mark.parametrize("g", [1.0, -0.3, 1e-30])
+def test_one_pass_matches_two(n, g):
+    x = torch.randn(n, device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    for i, v in enumerate([math.inf, -math.inf, math.nan, 0.0, -0.0, 3.4e38, 1e-40][:n]):
+        x[i] = v
+    up = torch.tensor(g, dtype=torch.float64, device="cuda")
+    with torch.no_grad():
+        got = _scaled_to_bf16(x, up)
+    want = torch.mul(x, up.to(torch.float32)).to(torch.bfloat16)
+    assert torch.equal(got.isnan(), want.isnan())
+    assert torch.equal(got.nan_to_num(), want.nan_to_num())
+
+
+def test_other_forms_go_through_torch():
+    x = torch.randn(16, 8, device="cuda")
+    up = torch.tensor(0.5, dtype=torch.float64, device="cuda")
+    want = (x * 0.5).to(torch.bfloat16)
+    with torch.no_grad():
+        assert torch.equal(_scaled_to_bf16(x.t().contiguous().t(), up), want)  # strided
+        odd = torch.empty(16 * 8 + 1, device="cuda")[1:].view(16, 8).copy_(x)  # not 16-byte aligned
+        assert torch.equal(_scaled_to_bf16(odd, up), want)
+        ups = torch.tensor([0.5, 2.0], dtype=torch.float64, device="cuda")
+        got = torch.func.vmap(lambda u: _scaled_to_bf16(x, u))(ups)  # batched upstream gradients
+        assert torch.equal(got[0], want) and torch.equal(got[1], (x * 2).to(torch.bfloat16))
+    up2 = up.clone().requires_grad_(True)  # a graph through the backward
+    _scaled_to_bf16(x, up2).float().sum().backward()
+    assert up2.grad is not None
