@@ -311,6 +311,35 @@ __device__ inline void merge_vocab_stats(const grpo_vocab_stats* stats, int n_sh
   za = z;
 }
 
+// merge_vocab_stats by a whole wave (all 64 lanes active), the same bits in every lane: lane g takes shard g's record
+// and its exponential, and the terms are added in shard order.  One lane's worth of fp64 exponentials per row and wave
+// instead of n_shards: with every wave of a row merging for itself, the serial form cost as much time as a short row's
+// traffic (8 shards, bf16, 32,768 rows, both calls: 9,000 columns 421 -> 346 us, 18,992 672 -> 662).
+__device__ inline void merge_vocab_stats_wave(const grpo_vocab_stats* stats, int n_shards, int T, int t, double& lse,
+                                              double& za) {
+  const int lane = threadIdx.x & 63;
+  double M = -INFINITY, z = -INFINITY, S = 0.0;
+  for (int g0 = 0; g0 < n_shards; g0 += 64) {
+    const int n = min(64, n_shards - g0);
+    grpo_vocab_stats r{-INFINITY, 0.0, -INFINITY};
+    if (lane < n) r = stats[(int64_t)(g0 + lane) * T + t];
+    for (int g = 0; g < n; ++g) {
+      const double m = readlane_f64(r.m, g);
+      if (m > M || isnan(m)) M = m;
+      z = fmax(z, readlane_f64(r.z_a, g));
+    }
+  }
+  for (int g0 = 0; g0 < n_shards; g0 += 64) {
+    const int n = min(64, n_shards - g0);
+    grpo_vocab_stats r{-INFINITY, 0.0, -INFINITY};
+    if (lane < n) r = stats[(int64_t)(g0 + lane) * T + t];
+    const double e = r.m != -INFINITY ? r.s * exp(r.m - M) : 0.0;
+    for (int g = 0; g < n; ++g) S += readlane_f64(e, g);
+  }
+  lse = row_lse(M, S);
+  za = z;
+}
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // max(a, b, c) in one instruction.  Written as asm because the compiler otherwise canonicalises every loaded

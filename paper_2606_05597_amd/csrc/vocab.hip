@@ -51,9 +51,10 @@ __device__ inline void shard_row_head(const ShardArgs& a, int t, RowScale& rs, i
 // The row's first U vectors per thread are loaded before the records are merged (the loads do not depend on
 // them), and every wave merges the records and forms the scale itself while they land: no barrier, no one-thread
 // section ahead of the loads.  Thread 0 alone writes the token's outputs.  RAG: rows that are not whole aligned
-// vectors (RowSplit).
+// vectors (RowSplit).  8 vectors: at least 4 waves per SIMD, or the compiler joins 8 fp32 vectors' exponentials into one
+// operation of 288 registers (both calls, 32,768 x 2,000 356 us, now 153).
 template <typename Tin, int NT, int U, bool RAG>
-__global__ __launch_bounds__(NT) void k_shard_rows_vec(const ShardArgs a) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(U == 8 ? 4 : 1))) void k_shard_rows_vec(const ShardArgs a) {
   const int t = blockIdx.x, tid = threadIdx.x;
   if (!a.dlogits) {  // forward only: the token's outputs, no row traffic
     if (tid == 0) {
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(NT) void k_shard_rows_vec(const ShardArgs a) {
     if (vi < nvec) x[u] = __builtin_nontemporal_load(src + vi);
   }
   double lse, za;
-  merge_vocab_stats(a.stats, a.n_shards, a.T, t, lse, za);
+  merge_vocab_stats_wave(a.stats, a.n_shards, a.T, t, lse, za);
   const TokenIn in = token_load(a.tok, t);
   TokenEval ev;
   const RowScale rs = token_eval(a.tok, in, lse, za, ev);
@@ -130,6 +131,25 @@ __global__ __launch_bounds__(256) void k_shard_rows_generic(const ShardArgs a) {
   }
 }
 
+// The vector kernel for rows of nvec vectors.  Every wave of a row merges the records and forms the scale, so short rows
+// take few waves: both calls of a shard step, bf16, T = 32,768, in us with 64 x 8 / 256 x 10 / 512 x 5 threads x vectors:
+// 2,000 columns 108 / 173 / 234, 4,000 161 / 197 / 252, 9,000 341 / 305 / 345, 12,000 440 / 414 / 421, 15,000 574 / 531 /
+// 514, 18,992 718 / 699 / 660.
+typedef void (*ShardKernel)(const ShardArgs);
+template <typename Tin>
+static ShardKernel shard_kernel(int64_t nvec, bool rag, int& nt) {
+  if (nvec <= 512) {
+    nt = 64;
+    return rag ? k_shard_rows_vec<Tin, 64, 8, true> : k_shard_rows_vec<Tin, 64, 8, false>;
+  }
+  if (nvec <= 1600) {
+    nt = 256;
+    return rag ? k_shard_rows_vec<Tin, 256, 10, true> : k_shard_rows_vec<Tin, 256, 10, false>;
+  }
+  nt = 512;
+  return rag ? k_shard_rows_vec<Tin, 512, 5, true> : k_shard_rows_vec<Tin, 512, 5, false>;
+}
+
 hipError_t launch_shard_rows(const void* logits, void* dlogits, grpo_dtype dt, int64_t T, int64_t V, int64_t ld,
                              int64_t v_begin, const grpo_vocab_stats* stats, int n_shards, const TokenArgs& tok,
                              hipStream_t s) {
@@ -146,18 +166,15 @@ hipError_t launch_shard_rows(const void* logits, void* dlogits, grpo_dtype dt, i
   a.tok = tok;
   const dim3 grid((unsigned)T);
   const bool bf = dt == GRPO_BF16;
-  switch (row_form(logits, dlogits, V, ld, bf ? 2 : 4)) {
-    case RowForm::kWhole:
-      if (bf) hipLaunchKernelGGL((k_shard_rows_vec<uint16_t, 512, 5, false>), grid, dim3(512), 0, s, a);
-      else hipLaunchKernelGGL((k_shard_rows_vec<float, 512, 5, false>), grid, dim3(512), 0, s, a);
-      break;
-    case RowForm::kRagged:
-      if (bf) hipLaunchKernelGGL((k_shard_rows_vec<uint16_t, 512, 5, true>), grid, dim3(512), 0, s, a);
-      else hipLaunchKernelGGL((k_shard_rows_vec<float, 512, 5, true>), grid, dim3(512), 0, s, a);
-      break;
-    default:
-      if (bf) hipLaunchKernelGGL(k_shard_rows_generic<uint16_t>, grid, dim3(256), 0, s, a);
-      else hipLaunchKernelGGL(k_shard_rows_generic<float>, grid, dim3(256), 0, s, a);
+  const RowForm form = row_form(logits, dlogits, V, ld, bf ? 2 : 4);
+  if (form == RowForm::kElements) {
+    if (bf) hipLaunchKernelGGL(k_shard_rows_generic<uint16_t>, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_shard_rows_generic<float>, grid, dim3(256), 0, s, a);
+  } else {
+    const bool rag = form == RowForm::kRagged;
+    int nt;
+    const ShardKernel k = bf ? shard_kernel<uint16_t>(V / 8, rag, nt) : shard_kernel<float>(V / 4, rag, nt);
+    hipLaunchKernelGGL(k, grid, dim3(nt), 0, s, a);
   }
   return hipGetLastError();
 }
