@@ -6,7 +6,7 @@
 // across the workgroup, and dlogits are formed from the same registers and
 // written once: V*s bytes read and V*s written per token.
 //
-//  k_rows_pipe      long bf16 rows (V up to 188,416): persistent, one
+//  k_rows_pipe      long bf16 rows (81,920 < V <= 188,416): persistent, one
 //                   workgroup of 1024 threads per CU.  Row t+G streams in
 //                   while row t's dlogits are written: part of each row lives
 //                   in LDS (global_load_lds), the rest in registers.
@@ -602,8 +602,11 @@ __global__ __launch_bounds__(1024) void k_rows_stream(const RowArgs a) {
 // ---- register-resident row kernel -------------------------------------------
 // NT threads per row, NV 16-byte vectors per thread: V/EPV <= NT*NV.  RAG: rows that
 // are not whole aligned vectors (RowSplit), otherwise they are (checked on the host).
+// 8 vectors: at least 4 waves per SIMD (128 registers).  Without the bound the compiler joins 8 fp32 vectors'
+// exponentials into one wide operation that takes 239: 30,000 x 6,000 459 us, now 279 (5.2 TB/s), 60,000 x 1,504 244,
+// now 141.  4 fp32 vectors are 1.5% faster without it.
 template <typename Tin, int NT, int NV, bool RAG>
-__global__ __launch_bounds__(NT) void k_rows_resident(const RowArgs a) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NV == 8 ? 4 : 1))) void k_rows_resident(const RowArgs a) {
   constexpr int NW = NT / 64;
   __shared__ float sh_m[NW];
   __shared__ double sh_s[NW];
@@ -763,8 +766,8 @@ static const Variant kVariants[] = {
 // that only each thread's last vector can be partial; NP vectors in LDS.
 #define GRPO_PIPE(NV, NP) {k_rows_pipe<NV, NP, false>, k_rows_pipe<NV, NP, true>}
 static const RowKernel kPipe[][2] = {
-    GRPO_PIPE(7, 4),  GRPO_PIPE(8, 4),  GRPO_PIPE(9, 5),  GRPO_PIPE(10, 5), GRPO_PIPE(11, 6), GRPO_PIPE(12, 6),
-    GRPO_PIPE(13, 7), GRPO_PIPE(14, 7), GRPO_PIPE(15, 1), GRPO_PIPE(16, 2), GRPO_PIPE(17, 3), GRPO_PIPE(18, 4),
+    GRPO_PIPE(11, 6), GRPO_PIPE(12, 6), GRPO_PIPE(13, 7), GRPO_PIPE(14, 7), GRPO_PIPE(15, 1), GRPO_PIPE(16, 2),
+    GRPO_PIPE(17, 3), GRPO_PIPE(18, 4),
     GRPO_PIPE(19, 6), GRPO_PIPE(20, 9), GRPO_PIPE(21, 9), GRPO_PIPE(22, 9), GRPO_PIPE(23, 9),
 };  // from 15 vectors on, 14 in registers and the rest in LDS, except 19 (V = 151,936): 13 and 6, 0.3% faster
    // than 15 and 4 and 0.4% faster than 14 and 5, with 12 and 7 or 11 and 8 within 0.1% of it (before the LDS
@@ -778,7 +781,9 @@ static const RowKernel kStreamRows[2] = {k_rows_stream<uint16_t, 9, 12, 4, false
 constexpr int64_t kStreamMaxRow = (int64_t)1 << 22;
 // k_rows_twice: rows addressed with 32-bit offsets.
 constexpr int64_t kTwiceMaxRow = (int64_t)1 << 30;
-constexpr int kPipeMinNV = 7, kPipeMaxNV = 23;  // at most 15 register vectors and 9 LDS vectors per thread
+// Up to 10 vectors the resident kernel is faster: persistent / resident, 30,000 x 50,000 1.34 / 1.15 ms, 20,000 x 60,000
+// 0.98 / 0.91, 20,000 x 80,000 1.24 / 1.18; at 11 and 12 1.09 / 1.10 (15,000 x 90,000), at 13 and 14 5% slower.
+constexpr int kPipeMinNV = 11, kPipeMaxNV = 23;  // at most 15 register vectors and 9 LDS vectors per thread
 constexpr int64_t kPipeMaxT = (int64_t)1 << 30;  // t + (gridDim.x - 1) * chunk + 1 stays far below 2^31
 
 struct Launch {

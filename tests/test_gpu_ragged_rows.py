@@ -51,7 +51,8 @@ def _loss(cfg, st, lg, act, behave, adv, V, dl, gs):
 # first and last sizes and one between two of its vector counts, a padded head, past it (the streaming kernel); fp32
 # rows, in the loss element by element, staged in LDS (up to 20,224 elements) or not; bf16 beyond 4 MiB (two passes)
 SIZES = [(1, 1, "bf16"), (7, 7, "bf16"), (8, 9, "bf16"), (519, 519, "bf16"), (8199, 8201, "bf16"), (32003, 32003, "bf16"),
-         (49159, 49159, "bf16"), (49161, 49162, "bf16"), (57353, 57353, "bf16"), (151669, 151936, "bf16"),
+         (49159, 49159, "bf16"), (49161, 49162, "bf16"), (57353, 57353, "bf16"), (81927, 81927, "bf16"),
+         (81929, 81929, "bf16"), (151669, 151936, "bf16"),
          (188423, 188423, "bf16"), (188431, 188431, "bf16"), (3, 3, "f32"), (259, 261, "f32"), (4093, 4093, "f32"),
          (77825, 77825, "f32"), (77831, 77832, "f32"), (20223, 20223, "f32"), (20225, 20225, "f32"),
          (151669, 151936, "f32"), (2097159, 2097159, "bf16"), (2097161, 2097161, "bf16")]
@@ -81,7 +82,7 @@ def test_loss_rows(V, ld, dtype, offset):
         assert (dl[:, V:] == 7.0).all()  # columns past V are left alone
 
 
-@pytest.mark.parametrize("V,T,dtype", [(57353, 1200, "bf16"), (188435, 600, "bf16"), (188440, 600, "bf16"),
+@pytest.mark.parametrize("V,T,dtype", [(57353, 300, "bf16"), (81929, 600, "bf16"), (90121, 1200, "bf16"), (188435, 600, "bf16"), (188440, 600, "bf16"),
                                        (77832, 600, "f32"), (77831, 300, "f32")])
 def test_dlogits_over_the_logits(V, T, dtype):
     # bf16: several rows per workgroup, edges and vector counts changing from row to row; fp32: the kernel that reads a
