@@ -36,14 +36,24 @@ def _apply_upstream(mode, grads, grad_output):
 
 
 def _plain(t):
-    """A tensor whose memory a kernel may be handed: no subclass, not batched or otherwise wrapped by a transform."""
-    return type(t) is torch.Tensor and not torch._C._functorch.is_functorch_wrapped_tensor(t) and t.is_cuda
+    """A tensor whose memory a kernel may be handed: no subclass, not batched or otherwise wrapped by a transform, its
+    values as they lie in memory."""
+    return (type(t) is torch.Tensor and not torch._C._functorch.is_functorch_wrapped_tensor(t) and t.is_cuda
+            and not t.is_neg())
+
+
+def _watched():
+    """Whether something follows the torch operations made now: a graph, forward-mode derivatives, a dispatch mode
+    (fake tensors, a tracer, a flop counter), a trace or the compiler."""
+    return (torch.is_grad_enabled() or torch.autograd.forward_ad._current_level >= 0
+            or torch._C._len_torch_dispatch_stack() > 0 or torch._C._get_tracing_state() is not None
+            or torch.compiler.is_compiling())
 
 
 def _scaled_to_bf16(t, grad_output):
-    """(t * grad_output in fp32) rounded to bf16, in one pass over t where nothing has to see the two operations: no
-    graph of the backward, no transform of it, a plain contiguous t as the library wrote it."""
-    if (torch.is_grad_enabled() or torch.compiler.is_compiling() or not (_plain(t) and _plain(grad_output))
+    """(t * grad_output in fp32) rounded to bf16, in one pass over t where nothing has to see the two operations
+    (_watched, _plain), a contiguous t as the library wrote it."""
+    if (_watched() or not (_plain(t) and _plain(grad_output))
             or t.dtype != torch.float32 or not t.is_contiguous() or t.data_ptr() % 16 or grad_output.numel() != 1
             or grad_output.device != t.device):
         return torch.mul(t, grad_output.to(t.dtype)).to(torch.bfloat16)

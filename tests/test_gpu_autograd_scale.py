@@ -38,3 +38,30 @@ def test_other_forms_go_through_torch():
     up2 = up.clone().requires_grad_(True)  # a graph through the backward
     _scaled_to_bf16(x, up2).float().sum().backward()
     assert up2.grad is not None
+
+
+def test_forward_mode_modes_and_lazy_negation_go_through_torch():
+    from torch.autograd import forward_ad
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Seen(TorchDispatchMode):
+        def __init__(self):
+            super().__init__()
+            self.ops = []
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.ops.append(func.__name__)
+            return func(*args, **(kwargs or {}))
+
+    x = torch.randn(16, 8, device="cuda")
+    up = torch.tensor(0.5, device="cuda")
+    with torch.no_grad():
+        with forward_ad.dual_level():  # the tangent of the upstream gradient reaches dW
+            out = _scaled_to_bf16(x, forward_ad.make_dual(up, torch.tensor(2.0, device="cuda")))
+            tangent = forward_ad.unpack_dual(out).tangent
+            assert tangent is not None and torch.equal(tangent, (x * 2).to(torch.bfloat16))
+        with Seen() as seen:
+            _scaled_to_bf16(x, up)
+        assert any("mul" in op for op in seen.ops)
+        neg = torch._neg_view(up)  # -0.5 over memory that holds 0.5
+        assert torch.equal(_scaled_to_bf16(x, neg), (x * -0.5).to(torch.bfloat16))
