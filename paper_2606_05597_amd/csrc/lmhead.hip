@@ -697,7 +697,10 @@ __device__ __forceinline__ void lm_dw_tile(const DwArgs& p, int bid, int nblocks
   g_f32x16 acc[LmCfg::IB][LmCfg::JB];
   gemm_mainloop_packed<LmCfg>(p.g, m0, n0, acc, sm.s);
   // Per 32-row block i: with accumulate, all of its old values are loaded first and waited for once, then
-  // added and stored (element by element, every load would wait for the memory in turn).
+  // added and stored (element by element, every load would wait for the memory in turn).  Without it the stores pass
+  // the L2 by, which keeps the h^T and D^T panels of the tiles beside: the fused call and its backward at 3,584 x
+  // 151,936 take 3.475 / 3.437 ms with cached / these stores at 700 rows, 2.64 / 2.60 at 300, 2.050 / 2.060 at 64 (the
+  // call alone 1.470 / 1.454), the same at 16,384; 1,024 x 32,000 at 300 rows 0.227 / 0.220.
   auto store = [&](auto full, auto accumulate) {
 #pragma unroll
     for (int i = 0; i < LmCfg::IB; ++i) {
@@ -720,7 +723,8 @@ __device__ __forceinline__ void lm_dw_tile(const DwArgs& p, int bid, int nblocks
 #pragma unroll
         for (int j = 0; j < LmCfg::JB; ++j) {
           if (!full && n0 + gemm_col<LmCfg>(wn, j, lane) >= p.g.N) continue;
-          o[32 * j] = accumulate ? old[r][j] + acc[i][j][r] : acc[i][j][r];
+          if (accumulate) o[32 * j] = old[r][j] + acc[i][j][r];
+          else __builtin_nontemporal_store(acc[i][j][r], o + 32 * j);
         }
       }
     }
