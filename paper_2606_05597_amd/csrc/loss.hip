@@ -129,7 +129,7 @@ __device__ __forceinline__ u32x4 vec_dlogits_kept(const u32x4& e, float c, bool 
   return o;
 }
 
-// Combines every thread's (max m, sum s of exp(z - m)) into the row's (M, S),
+// Combines every thread's (shift m >= kShiftMin, sum s of exp(z - m)) into the row's (M, S),
 // valid in thread 0: within each wave (DPP within rows of 16 lanes, then the
 // four rows), then across the NW <= 16 waves by the first 16 lanes of wave 0,
 // one wave partial per lane.  The rescale factors exp(m - M) <= 1 are fp32 and
@@ -141,8 +141,7 @@ __device__ __forceinline__ void block_combine(float m, float s, float* sh_m, dou
   static_assert(NW >= 1 && NW <= 16, "one wave partial per lane of a 16-lane row");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const float mw = wave_max_dpp(m);
-  const double sw =
-      wave_sum_dpp((m == -INFINITY) ? 0.0 : (double)s * (double)__builtin_amdgcn_exp2f((m - mw) * kLog2e));
+  const double sw = wave_sum_dpp((double)s * (double)__builtin_amdgcn_exp2f((m - mw) * kLog2e));
   if (lane == 0) {
     sh_m[wv] = mw;
     sh_s[wv] = sw;
@@ -166,8 +165,7 @@ __device__ __forceinline__ void block_combine_all(float m, float s, float* sh_m,
   static_assert(NW >= 1 && NW <= 16, "one wave partial per lane of a 16-lane row");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = lane & 15;
   const float mw = wave_max_dpp(m);
-  const double sw =
-      wave_sum_dpp((m == -INFINITY) ? 0.0 : (double)s * (double)__builtin_amdgcn_exp2f((m - mw) * kLog2e));
+  const double sw = wave_sum_dpp((double)s * (double)__builtin_amdgcn_exp2f((m - mw) * kLog2e));
   if (lane == 0) {
     sh_m[wv] = mw;
     sh_s[wv] = sw;
@@ -710,7 +708,7 @@ __global__ __launch_bounds__(256) void k_rows_elements(const RowArgs a) {
       }
     }
   };
-  float m = -INFINITY;
+  float m = kShiftMin;
   if (staged)
     sweep(std::false_type(), [&](int64_t v, Tin z) {
       stage[v] = z;  // read back by the same thread
@@ -718,7 +716,7 @@ __global__ __launch_bounds__(256) void k_rows_elements(const RowArgs a) {
     });
   else
     sweep(std::false_type(), [&](int64_t, Tin z) { m = fmaxf(m, load_elem(&z)); });
-  const float nmb = (m == -INFINITY) ? 0.f : -m * kLog2e;
+  const float nmb = -m * kLog2e;
   float s = 0.f;
   auto add = [&](int64_t, Tin z) { s += __builtin_amdgcn_exp2f(fmaf(load_elem(&z), kLog2e, nmb)); };
   if (staged) sweep(std::true_type(), add);

@@ -119,22 +119,29 @@ def test_logp_and_records(V, ld, dtype, offset):
     np.testing.assert_allclose(s, want.s, rtol=5e-6)
 
 
+@pytest.mark.parametrize("left", [300, 100, 1])
 @pytest.mark.parametrize("V,ld,dtype", [(1003, 1003, "bf16"), (1003, 1003, "f32"), (32003, 32003, "bf16"),
-                                        (57353, 57353, "bf16"), (77831, 77831, "f32"), (1000, 1000, "bf16")])
-def test_logits_masked_with_the_lowest_value(V, ld, dtype):
-    # all but the last 300 columns at the type's lowest value, as masks often are: they carry no probability, whole
-    # threads' shares of a row among them
+                                        (57353, 57353, "bf16"), (77831, 77831, "f32"), (1000, 1000, "bf16"),
+                                        (1000, 1000, "f32"), (1004, 1004, "f32"), (131, 131, "f32"),
+                                        (20225, 20225, "f32"), (77832, 77832, "f32"), (188440, 188440, "bf16")])
+def test_logits_masked_with_the_lowest_value(V, ld, dtype, left):
+    # all but the last `left` columns at the type's lowest value, as masks often are: they carry no probability.  With
+    # fewer columns left than a row's kernel has threads, some thread's whole share of the row is masked.  dlogits at
+    # the logits' distance from a 16-byte boundary and at another (the kernel that takes rows element by element)
+    left = min(left, V - 30)
     cfg, st, lg, act, behave, adv = _batch(V, ld, dtype, 0)
-    lg[:, :V - 300] = torch.finfo(lg.dtype).min
-    act = act % 300 + (V - 300)
-    z = lg[:, V - 300:V].double()
+    lg[:, :V - left] = torch.finfo(lg.dtype).min
+    act = act % left + (V - left)
+    z = lg[:, V - left:V].double()
     lse = torch.logsumexp(z, 1)
-    want = z.gather(1, (act.long() - (V - 300))[:, None])[:, 0] - lse
+    want = z.gather(1, (act.long() - (V - left))[:, None])[:, 0] - lse
     logp, ent = grpo.grpo_token_logp(lg, act, V=V)
     assert (logp.double() - want).abs().max().item() <= LOGP_ATOL
     p = torch.exp(z - lse[:, None])
     assert (ent.double() + (p * (z - lse[:, None])).sum(1)).abs().max().item() <= 4e-4
-    dl = torch.empty_like(lg)
-    _, aux = _loss(cfg, st, lg, act, want.float(), adv, V, dl, 1.0)
-    assert (aux.token_logp.double() - want).abs().max().item() <= LOGP_ATOL and aux.error_flags.item() == 0
-    assert (dl[:, :V - 300] == 0).all() and torch.isfinite(dl).all()
+    T = len(act)
+    for shift in (0, 1):
+        dl = torch.full((T * ld + 32,), 7.0, dtype=lg.dtype, device="cuda")[shift:shift + T * ld].view(T, ld)
+        _, aux = _loss(cfg, st, lg, act, want.float(), adv, V, dl, 1.0)
+        assert (aux.token_logp.double() - want).abs().max().item() <= LOGP_ATOL and aux.error_flags.item() == 0
+        assert (dl[:, :V - left] == 0).all() and torch.isfinite(dl).all()
