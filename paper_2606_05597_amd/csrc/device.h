@@ -352,10 +352,12 @@ __device__ __forceinline__ float max3f(float a, float b, float c) {
   return r;
 }
 
-// The lowest exp shift m of a thread's sum of e^(z - m): -m log2(e) stays finite, so that logits masked with the
-// type's lowest value add 0 as -inf does (at m = -3.4e38 their terms were inf, and the row's sum NaN).  A row with
-// nothing above it has the sum 0.
-constexpr float kShiftMin = -1e38f;
+// The lowest exp shift m of a thread's sum of e^(z - m), so that logits masked with any large negative number add 0 as
+// -inf does.  A term's argument is z log2(e) less the rounded m log2(e): at z = m it is the rounding's error, up to 8 at
+// m = -1e8 but large enough for an infinite term at -1e10 (and m log2(e) itself overflows at the type's lowest value),
+// and a thread whose whole share of the row is masked then made the row's sum NaN; from 16 on, the fp16 terms that a
+// row keeps in LDS overflowed.  A row with nothing above it has the sum 0.
+constexpr float kShiftMin = -1e8f;
 
 // Maximum of m and the vector's elements (the exp shift of the row).
 template <typename Tin>

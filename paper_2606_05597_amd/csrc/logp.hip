@@ -47,12 +47,13 @@ __device__ __forceinline__ void fold(float z, float nmb, float& s, float& t) {
   if constexpr (ENT) t = fmaf(e, fmaxf(w, -FLT_MAX), t);
 }
 
-// Raises the shift m >= kShiftMin to mn: s and t are re-expressed relative to mn.
+// Raises the shift m >= kShiftMin to mn: s and t are re-expressed relative to mn.  Where nothing is left of the old sum
+// (f = 0) its moment is 0 too: -dl s may then be infinite.
 template <bool ENT = true>
 __device__ __forceinline__ void rescale(float& m, float mn, float& s, float& t) {
   if (mn > m) {
     const float dl = (mn - m) * kLog2e, f = __builtin_amdgcn_exp2f(-dl);
-    if constexpr (ENT) t = f * fmaf(-dl, s, t);
+    if constexpr (ENT) t = f == 0.f ? 0.f : f * fmaf(-dl, s, t);
     s *= f;
     m = mn;
   }

@@ -119,18 +119,21 @@ def test_logp_and_records(V, ld, dtype, offset):
     np.testing.assert_allclose(s, want.s, rtol=5e-6)
 
 
-@pytest.mark.parametrize("left", [300, 100, 1])
+@pytest.mark.parametrize("mask,left", [(None, 300), (None, 100), (None, 1), (-1e8, 100), (-1e9, 100), (-1e10, 100),
+                                       (-1e30, 1), (-1e38, 100), (-2.3819763e38, 100)])
 @pytest.mark.parametrize("V,ld,dtype", [(1003, 1003, "bf16"), (1003, 1003, "f32"), (32003, 32003, "bf16"),
                                         (57353, 57353, "bf16"), (77831, 77831, "f32"), (1000, 1000, "bf16"),
                                         (1000, 1000, "f32"), (1004, 1004, "f32"), (131, 131, "f32"),
-                                        (20225, 20225, "f32"), (77832, 77832, "f32"), (188440, 188440, "bf16")])
-def test_logits_masked_with_the_lowest_value(V, ld, dtype, left):
-    # all but the last `left` columns at the type's lowest value, as masks often are: they carry no probability.  With
-    # fewer columns left than a row's kernel has threads, some thread's whole share of the row is masked.  dlogits at
-    # the logits' distance from a 16-byte boundary and at another (the kernel that takes rows element by element)
+                                        (20225, 20225, "f32"), (77832, 77832, "f32"), (151936, 151936, "bf16"),
+                                        (188440, 188440, "bf16")])
+def test_logits_masked_with_the_lowest_value(V, ld, dtype, mask, left):
+    # all but the last `left` columns at the type's lowest value or another large negative one, as masks often are: they
+    # carry no probability.  With fewer columns left than a row's kernel has threads, some thread's whole share of the
+    # row is masked.  dlogits at the logits' distance from a 16-byte boundary and at another (the kernel that takes rows
+    # element by element)
     left = min(left, V - 30)
     cfg, st, lg, act, behave, adv = _batch(V, ld, dtype, 0)
-    lg[:, :V - left] = torch.finfo(lg.dtype).min
+    lg[:, :V - left] = torch.finfo(lg.dtype).min if mask is None else mask
     act = act % left + (V - left)
     z = lg[:, V - left:V].double()
     lse = torch.logsumexp(z, 1)
