@@ -44,9 +44,10 @@ def _plain(t):
 
 def _watched():
     """Whether something follows the torch operations made now: a graph, forward-mode derivatives, a dispatch mode
-    (fake tensors, a tracer, a flop counter), a trace or the compiler."""
+    (fake tensors, a tracer, a flop counter), a function mode, a trace or the compiler."""
     return (torch.is_grad_enabled() or torch.autograd.forward_ad._current_level >= 0
-            or torch._C._len_torch_dispatch_stack() > 0 or torch._C._get_tracing_state() is not None
+            or torch._C._len_torch_dispatch_stack() > 0 or torch._C._len_torch_function_stack() > 0
+            or torch._C._get_tracing_state() is not None
             or torch.compiler.is_compiling())
 
 

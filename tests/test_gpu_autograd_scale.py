@@ -65,3 +65,23 @@ def test_forward_mode_modes_and_lazy_negation_go_through_torch():
         assert any("mul" in op for op in seen.ops)
         neg = torch._neg_view(up)  # -0.5 over memory that holds 0.5
         assert torch.equal(_scaled_to_bf16(x, neg), (x * -0.5).to(torch.bfloat16))
+
+
+def test_function_modes_go_through_torch():
+    from torch.overrides import TorchFunctionMode
+
+    class Seen(TorchFunctionMode):
+        def __init__(self):
+            super().__init__()
+            self.calls = []
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.calls.append(func.__name__)
+            return func(*args, **(kwargs or {}))
+
+    x = torch.randn(16, 8, device="cuda")
+    up = torch.tensor(0.5, device="cuda")
+    with torch.no_grad():
+        with Seen() as seen:
+            got = _scaled_to_bf16(x, up)
+        assert "mul" in seen.calls and torch.equal(got, (x * 0.5).to(torch.bfloat16))
