@@ -37,9 +37,9 @@ def _apply_upstream(mode, grads, grad_output):
 
 def _plain(t):
     """A tensor whose memory a kernel may be handed: no subclass, not batched or otherwise wrapped by a transform, its
-    values as they lie in memory."""
+    values as they lie in memory (a zero tensor has none)."""
     return (type(t) is torch.Tensor and not torch._C._functorch.is_functorch_wrapped_tensor(t) and t.is_cuda
-            and not t.is_neg())
+            and not t.is_neg() and not t._is_zerotensor())
 
 
 def _watched():

@@ -85,3 +85,10 @@ def test_function_modes_go_through_torch():
         with Seen() as seen:
             got = _scaled_to_bf16(x, up)
         assert "mul" in seen.calls and torch.equal(got, (x * 0.5).to(torch.bfloat16))
+
+
+def test_an_upstream_gradient_without_memory():
+    x = torch.randn(16, 8, device="cuda")
+    zero = torch._efficientzerotensor((), device="cuda")  # known to be zero: no storage behind it
+    with torch.no_grad():
+        assert torch.equal(_scaled_to_bf16(x, zero) + 0, torch.zeros_like(x, dtype=torch.bfloat16))
