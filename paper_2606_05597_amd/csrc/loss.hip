@@ -779,6 +779,16 @@ static const RowKernel kStreamRows[2] = {k_rows_stream<uint16_t, 9, 12, 4, false
 constexpr int64_t kStreamMaxRow = (int64_t)1 << 22;
 // k_rows_twice: rows addressed with 32-bit offsets.
 constexpr int64_t kTwiceMaxRow = (int64_t)1 << 30;
+// Rows without dlogits: a record pass reads a row once, at eight workgroups to a CU, where the kernels that hold most of
+// a row read its end a second time and form dlogits for nobody.  They pay while the rows are too few to fill the chip.
+// The loss alone, record pass and epilogue / the kernel that holds the row, in us, on 256 CUs:
+//   bf16 (k_rows_stream) 200,000 columns, 128 rows 41 / 37, 300 44 / 64, 3,000 195 / 316; 2,097,152 columns, 128 rows
+//   308 / 240, 300 331 / 534
+//   fp32 (k_rows_twice) 151,936 columns, 400 rows 54 / 45, 520 60 / 68, 3,000 281 / 286; 1,000,000 columns, 400 rows
+//   280 / 273, 520 319 / 436, 3,000 1,792 / 1,916; up to 512 KB a row 100,000 columns, 700 rows 53 / 51, 3,000 192 / 190
+static bool records_without_dlogits(grpo_dtype dt, int64_t T, int64_t V, int n_cu) {
+  return dt == GRPO_BF16 ? T > n_cu / 2 : T > n_cu + n_cu / 2 && V > 131072;
+}
 // Up to 10 vectors the resident kernel is faster: persistent / resident, 30,000 x 50,000 1.34 / 1.15 ms, 20,000 x 60,000
 // 0.98 / 0.91, 20,000 x 80,000 1.24 / 1.18; at 11 and 12 1.09 / 1.10 (15,000 x 90,000), at 13 and 14 5% slower.
 constexpr int kPipeMinNV = 11, kPipeMaxNV = 23;  // at most 15 register vectors and 9 LDS vectors per thread
@@ -789,7 +799,8 @@ struct Launch {
   int nt;
   unsigned grid;
   int chunk = 1, r0 = 0, chunk2 = 1;
-  unsigned lds = 0;  // dynamic LDS bytes
+  unsigned lds = 0;    // dynamic LDS bytes
+  bool twice = false;  // without k: k_rows_twice
 };
 
 static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, const void* logits,
@@ -805,13 +816,15 @@ static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, c
     const int64_t nvec = V / epv;  // the most a row has
     const int64_t nv = (nvec + 1023) / 1024;
     RowKernel k = nullptr;
+    int n_cu = stream_cu_count(s);  // of the stream's device
+    if (n_cu < 1) n_cu = 256;
     if (T <= kPipeMaxT) {
       if (dt == GRPO_BF16 && nv >= kPipeMinNV && nv <= kPipeMaxNV) k = kPipe[nv - kPipeMinNV][rag];
-      else if (dt == GRPO_BF16 && nv > kPipeMaxNV && nvec * 16 <= kStreamMaxRow) k = kStreamRows[rag];
+      else if (dt == GRPO_BF16 && nv > kPipeMaxNV && nvec * 16 <= kStreamMaxRow &&
+               (dlogits || !records_without_dlogits(dt, T, V, n_cu)))
+        k = kStreamRows[rag];
     }
     if (k) {
-      int n_cu = stream_cu_count(s);  // of the stream's device
-      if (n_cu < 1) n_cu = 256;
       // chunks of up to 8 rows (1.6-2.5% faster than single rows at 120,000 x 151,936), but at least four chunks
       // per CU, so that small batches still spread over the chip
       const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(8, T / (4 * (int64_t)n_cu)));
@@ -826,7 +839,9 @@ static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, c
     for (const Variant& v : kVariants) {
       if ((int64_t)v.nt * v.nv >= nvec) return Launch{dt == GRPO_BF16 ? v.bf16[rag] : v.f32, v.nt, (unsigned)T};
     }
-    return Launch{nullptr, 0, 0};  // two passes
+    Launch l{nullptr, 0, 0};  // two passes, or fp32 rows in one
+    l.twice = dt == GRPO_F32 && V * 4 <= kTwiceMaxRow && (dlogits || !records_without_dlogits(dt, T, V, n_cu));
+    return l;
   }
   // staged in LDS where two workgroups fit a CU: alone on its CU, 256 threads took 0.96 ms at fp32 10,000 x 32,003
   // against 0.80 with every sweep from memory
@@ -890,7 +905,7 @@ extern "C" int grpo_loss_fwd_bwd(const void* logits, int32_t dtype, int64_t T, i
     if (k.k) {
       hipLaunchKernelGGL(k.k, dim3(k.grid), dim3(k.nt), k.lds, s, a);
       if (hipGetLastError() != hipSuccess) return GRPO_ERR_HIP;
-    } else if (dt == GRPO_F32 && V * 4 <= kTwiceMaxRow) {
+    } else if (k.twice) {
       if (launch_rows_twice(logits, dlogits, T, ld, a.tok, s) != hipSuccess) return GRPO_ERR_HIP;
     } else {
       // the whole vocabulary as one shard: its records, then the merge (trivial), epilogue and dlogits

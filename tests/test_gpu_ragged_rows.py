@@ -148,3 +148,21 @@ def test_logits_masked_with_the_lowest_value(V, ld, dtype, mask, left):
         _, aux = _loss(cfg, st, lg, act, want.float(), adv, V, dl, 1.0)
         assert (aux.token_logp.double() - want).abs().max().item() <= LOGP_ATOL and aux.error_flags.item() == 0
         assert (dl[:, :V - left] == 0).all() and torch.isfinite(dl).all()
+
+
+@pytest.mark.parametrize("V,ld,T,dtype", [(188440, 188440, 128, "bf16"), (188440, 188440, 129, "bf16"),
+                                          (188443, 188443, 129, "bf16"), (77828, 77828, 400, "f32"),
+                                          (131076, 131076, 384, "f32"), (131076, 131076, 385, "f32"),
+                                          (151936, 151936, 40, "bf16"), (65536, 65536, 40, "bf16"),
+                                          (32003, 32003, 40, "f32")])
+def test_loss_alone(V, ld, T, dtype):
+    # no dlogits: every row kernel, and on both sides of the number of rows (on 256 CUs) from which long rows are read
+    # once by their record pass
+    cfg, st, lg, act, behave, adv = _batch(V, ld, dtype, 0, T=T)
+    z = lg[:, :V].double()
+    want = z.gather(1, act.long()[:, None])[:, 0] - torch.logsumexp(z, 1)
+    loss, aux = _loss(cfg, st, lg, act, behave, adv, V, False, 1.0)
+    assert (aux.token_logp.double() - want).abs().max().item() <= LOGP_ATOL and aux.error_flags.item() == 0
+    both, aux2 = _loss(cfg, st, lg, act, behave, adv, V, torch.empty_like(lg), 1.0)
+    assert abs(loss - both) <= LOSS_RTOL * abs(both)
+    assert (aux.token_logp - aux2.token_logp).abs().max().item() <= LOGP_ATOL
