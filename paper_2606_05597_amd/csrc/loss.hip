@@ -777,8 +777,13 @@ static const RowKernel kStreamRows[2] = {k_rows_stream<uint16_t, 9, 12, 4, false
                                          k_rows_stream<uint16_t, 9, 12, 4, true>};
 // Rows of up to 4 MiB, beyond which the second read misses more and more (fp32 rows of 4 MB gained 6%).
 constexpr int64_t kStreamMaxRow = (int64_t)1 << 22;
-// k_rows_twice: rows addressed with 32-bit offsets.
+// k_rows_twice: rows addressed with 32-bit offsets, of up to 8 MB, or longer ones while there are too few to fill the
+// chip.  Loss and dlogits in two passes / here, ms: 8 MB a row, 600 rows 2.64 / 2.60, 2,100 9.40 / 9.48; 16 MB, 300 rows
+// 3.35 / 3.10, 600 5.41 / 5.58; 32 MB, 300 rows 6.66 / 6.26, 600 11.4 / 11.7.
 constexpr int64_t kTwiceMaxRow = (int64_t)1 << 30;
+static bool rows_twice(int64_t T, int64_t V, int n_cu) {
+  return V * 4 <= kTwiceMaxRow && (V * 4 <= (int64_t)8 << 20 || T <= n_cu + n_cu / 2);
+}
 // Rows without dlogits: a record pass reads a row once, at eight workgroups to a CU, where the kernels that hold most of
 // a row read its end a second time and form dlogits for nobody.  They pay while the rows are too few to fill the chip.
 // The loss alone, record pass and epilogue / the kernel that holds the row, in us, on 256 CUs:
@@ -840,7 +845,7 @@ static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, c
       if ((int64_t)v.nt * v.nv >= nvec) return Launch{dt == GRPO_BF16 ? v.bf16[rag] : v.f32, v.nt, (unsigned)T};
     }
     Launch l{nullptr, 0, 0};  // two passes, or fp32 rows in one
-    l.twice = dt == GRPO_F32 && V * 4 <= kTwiceMaxRow && (dlogits || !records_without_dlogits(dt, T, V, n_cu));
+    l.twice = dt == GRPO_F32 && rows_twice(T, V, n_cu) && (dlogits || !records_without_dlogits(dt, T, V, n_cu));
     return l;
   }
   // staged in LDS where two workgroups fit a CU: alone on its CU, 256 threads took 0.96 ms at fp32 10,000 x 32,003

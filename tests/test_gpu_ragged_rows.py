@@ -166,3 +166,23 @@ def test_loss_alone(V, ld, T, dtype):
     both, aux2 = _loss(cfg, st, lg, act, behave, adv, V, torch.empty_like(lg), 1.0)
     assert abs(loss - both) <= LOSS_RTOL * abs(both)
     assert (aux.token_logp - aux2.token_logp).abs().max().item() <= LOGP_ATOL
+
+
+def test_fp32_rows_of_more_than_8_mb():
+    # on 256 CUs 384 such rows are read by the kernel that holds a part of them, 385 in two passes, to the same bits (the
+    # constant normaliser gives every token the same weight in both)
+    V, T = 2097156, 385
+    cfg, st, lg, act, behave, adv = _batch(V, V, "f32", 0, T=T)
+    got = []
+    for t in (T, T - 1):
+        st.step_tok_off[-1] = t
+        dl = torch.empty_like(lg[:t])
+        _, aux = _loss(cfg, st, lg[:t], act[:t], behave[:t], adv, V, dl, 1.0)
+        assert aux.error_flags.item() == 0
+        got.append((dl, aux.token_logp))
+    assert torch.equal(got[0][0][:T - 1], got[1][0]) and torch.equal(got[0][1][:T - 1], got[1][1])
+    p = torch.softmax(lg[T - 1].double(), 0)
+    p[act[T - 1].item()] -= 1
+    d = got[0][0][T - 1].double()
+    g = d[act[T - 1].item()] / p[act[T - 1].item()]
+    assert (d - g * p).abs().max().item() <= 1e-5 * d.abs().max().item()
