@@ -246,8 +246,10 @@ __device__ __forceinline__ double block_ext(double v, double* sh) {
 // Latency-bound: a few hundred tokens per workgroup, then one workgroup over the trajectories.  Clip counts and ratio
 // statistics are formed for the calls that ask for them only, and a workgroup's four counts go into the header as two
 // 64-bit atomics (every count is below 2^31).  With four atomics from every wave, all on one line, and every statistic
-// reduced whether wanted or not, the launch took 32 us at T = 32,411 (every output asked for; 15 now) and 27 at
-// 30,000 (the loss alone; 7 now).
+// reduced whether wanted or not, the launch took 32 us at T = 32,411 (every output asked for) and 27 at 30,000 (the
+// loss alone; 7 now).  Every output is gathered in one walk over the tokens, four at a time: the whole loss call on
+// rows of 64 with every output took 69 us at 30,000 tokens in 8 trajectories and 492 at 100,000 in one with a walk for
+// each kind of output, and takes 37 and 125.
 __global__ __launch_bounds__(256) void k_reduce(const ReduceArgs a) {
   __shared__ double sh[4];
   __shared__ int64_t shc[4][2];
@@ -257,15 +259,52 @@ __global__ __launch_bounds__(256) void k_reduce(const ReduceArgs a) {
   const int64_t t0 = min(max((int64_t)a.traj_tok_off[i], (int64_t)0), a.T);
   const int64_t t1 = min(max((int64_t)a.traj_tok_off[i + 1], t0), a.T);
   double acc = 0.0;
-  for (int64_t t = t0 + tid; t < t1; t += 256) acc += a.contrib[t];
-  const double tot = block_sum<256>(acc, sh);
-  if (counts) {
-    int64_t c0 = 0, c1 = 0;  // eps-clip cut and dual-clip cut, ratio outside and valid: low and high halves
-    for (int64_t t = t0 + tid; t < t1; t += 256) {
-      const int st = a.state[t];
+  double sr = 0.0, srho = 0.0;
+  double rmin = INFINITY, rmax = -INFINITY, pmin = INFINITY, pmax = -INFINITY;
+  int64_t c0 = 0, c1 = 0;  // eps-clip cut and dual-clip cut, ratio outside and valid: low and high halves
+  if (!counts) {
+    for (int64_t t = t0 + tid; t < t1; t += 256) acc += a.contrib[t];
+  } else {  // one walk: a trajectory's tokens are a chain of memory latencies, of which three walks take three
+    auto add = [&](double c, int st) {
+      acc += c;
       c0 += (int64_t)((st & kStateEpsCut) != 0) | ((int64_t)((st & kStateDualCut) != 0) << 32);
       c1 += (int64_t)((st & kStateOutside) != 0) | ((int64_t)((st & kStateValid) != 0) << 32);
+    };
+    auto add_ratios = [&](double2 q, int st) {
+      if (!(st & kStateValid)) return;
+      sr += q.x;
+      srho += q.y;
+      rmin = fmin(rmin, q.x);
+      rmax = fmax(rmax, q.x);
+      pmin = fmin(pmin, q.y);
+      pmax = fmax(pmax, q.y);
+    };
+    constexpr int U = 4;  // tokens in flight
+    int64_t t = t0 + tid;
+    for (; t + (U - 1) * 256 < t1; t += U * 256) {
+      double c[U];
+      double2 q[U];
+      int st[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        c[u] = a.contrib[t + u * 256];
+        st[u] = a.state[t + u * 256];
+        if (ratios) q[u] = a.tok_ratio[t + u * 256];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        add(c[u], st[u]);
+        if (ratios) add_ratios(q[u], st[u]);
+      }
     }
+    for (; t < t1; t += 256) {
+      const int st = a.state[t];
+      add(a.contrib[t], st);
+      if (ratios) add_ratios(a.tok_ratio[t], st);
+    }
+  }
+  const double tot = block_sum<256>(acc, sh);
+  if (counts) {
     c0 = wave_sum_i64(c0);
     c1 = wave_sum_i64(c1);
     if ((tid & 63) == 0) {
@@ -279,18 +318,6 @@ __global__ __launch_bounds__(256) void k_reduce(const ReduceArgs a) {
     }
   }
   if (ratios) {
-    double sr = 0.0, srho = 0.0;
-    double rmin = INFINITY, rmax = -INFINITY, pmin = INFINITY, pmax = -INFINITY;
-    for (int64_t t = t0 + tid; t < t1; t += 256) {
-      if (!(a.state[t] & kStateValid)) continue;
-      const double2 q = a.tok_ratio[t];
-      sr += q.x;
-      srho += q.y;
-      rmin = fmin(rmin, q.x);
-      rmax = fmax(rmax, q.x);
-      pmin = fmin(pmin, q.y);
-      pmax = fmax(pmax, q.y);
-    }
     const double tsr = block_sum<256>(sr, sh), tsrho = block_sum<256>(srho, sh);
     const double trmin = block_ext<256, false>(rmin, sh), trmax = block_ext<256, true>(rmax, sh);
     const double tpmin = block_ext<256, false>(pmin, sh), tpmax = block_ext<256, true>(pmax, sh);

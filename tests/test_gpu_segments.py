@@ -54,3 +54,38 @@ def test_tables_and_reduction(n_traj, max_steps, norm):
             assert (aux.gather_idx.cpu().numpy() == oracle.gather_index(T, V, act.cpu().numpy())).all()
             np.testing.assert_allclose(aux.traj_loss.cpu().numpy(), ref.traj_loss, rtol=LOSS_RTOL,
                                        atol=LOSS_RTOL * np.abs(ref.traj_loss).max())
+
+
+def test_long_trajectories():
+    """Trajectories on both sides of the reduction's 1,024 tokens at a time, a token outside the loss in each."""
+    G, V, toks = 5, 64, [1, 769, 1024, 1025, 2777]
+    sto = np.concatenate([[0], np.cumsum(toks)]).astype(np.int32)
+    tso = np.arange(G + 1, dtype=np.int32)
+    T = int(sto[-1])
+    lg = torch.randn((T, V), generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    act = torch.randint(0, V, (T,), generator=torch.Generator("cuda").manual_seed(3), device="cuda", dtype=torch.int32)
+    lp = torch.log_softmax(lg, 1).gather(1, act.long()[:, None])[:, 0]
+    act[torch.from_numpy(sto[1:] - 1).long().cuda()] = V  # each trajectory's last token
+    behave = lp + 0.3 * torch.randn(T, generator=torch.Generator("cuda").manual_seed(2), device="cuda")
+    adv = oracle.advantages(np.array([1, 0, 1, 0, 0], np.float32), G).astype(np.float32)
+    seg = oracle.segments(T, sto, tso)
+    ref = oracle.loss_rows(to_np_logits(lg), act.cpu().numpy(), behave.cpu().numpy(), None, adv.astype(np.float64),
+                           seg, G, norm=oracle.NORM_CONST_K, k=5.0, dual_clip_c=3.0)
+    valid = oracle.valid_tokens(act.cpu().numpy(), V, seg)
+    want = oracle.ratio_stats(ref.token_logp, behave.cpu().numpy(), None, valid)
+    for which in ((), ("clip_counts",), ("ratio_stats", "clip_counts", "traj_loss")):
+        aux = grpo.LossAux.alloc(T, G, "cuda", which=which)
+        loss, _ = grpo.grpo_loss_fwd_bwd(lg, act, behave, torch.from_numpy(adv).cuda(), torch.from_numpy(sto).cuda(),
+                                         torch.from_numpy(tso).cuda(), G, k=5.0, dual_clip_c=3.0,
+                                         aux=aux if which else None)
+        torch.cuda.synchronize()
+        assert abs(loss.item() - ref.loss) <= LOSS_RTOL * np.abs(ref.token_contrib).sum()
+        near = 2  # tokens whose fp64 ratio lies next to a boundary may fall either way
+        if aux.clip_counts is not None:
+            got = aux.clip_counts.cpu().numpy()
+            assert abs(got[0] - (ref.token_state & 1).sum()) <= near
+            assert abs(got[1] - ((ref.token_state >> 1) & 1).sum()) <= near
+        if aux.ratio_stats is not None:
+            got = aux.ratio_stats.cpu().numpy()
+            np.testing.assert_allclose(got[:6], want[:6], rtol=1e-5)
+            assert abs(got[6] - want[6]) <= near and got[7] == want[7] == T - G
