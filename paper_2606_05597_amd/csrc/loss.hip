@@ -674,14 +674,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NV == 8 ? 4 
 // ---- element row kernel --------------------------------------------------------
 // Any V, ld and element alignment, thread k of 256 on columns k, k + 256, ...: fp32 rows that are not whole aligned
 // vectors, and rows whose dlogits lie at another distance from a 16-byte boundary than their logits.  Three sweeps
-// (max, sum, dlogits) with U elements in flight; a row that fits the workgroup's dynamic LDS (stage_row) is read from
-// memory once and from there afterwards.  A thread's terms are summed one after the other in column order.
+// (max, sum, dlogits) with U elements in flight.  HELD: the row has at most U elements a thread, which stay in
+// registers; otherwise a row that fits the workgroup's dynamic LDS (stage_row) is read from memory once and from there
+// afterwards.  A thread's terms are summed one after the other in column order in every form.
 // Bound by the element accesses' rate and, unstaged, by the re-reads.  fp32 loss and dlogits with one element in flight
 // and every sweep from memory / here: 30,000 x 9,001 0.94 / 0.41 ms (5.3 TB/s), 20,000 x 19,003 1.32 / 0.71, 10,000 x
-// 32,003 1.26 / 0.80, 6,000 x 151,669 3.77 / 3.23.
-template <typename Tin>
+// 32,003 1.26 / 0.80, 6,000 x 151,669 3.77 / 3.23; of rows held, 20,000 x 101 50 / 34 us, x 1,003 78 / 48, x 2,003 165 /
+// 80.
+template <typename Tin, int U, bool HELD>
 __global__ __launch_bounds__(256) void k_rows_elements(const RowArgs a) {
-  constexpr int NT = 256, NW = NT / 64, U = 16;
+  constexpr int NT = 256, NW = NT / 64;
   extern __shared__ __attribute__((aligned(16))) char dyn[];
   Tin* stage = reinterpret_cast<Tin*>(dyn);
   __shared__ float sh_m[NW];
@@ -690,16 +692,23 @@ __global__ __launch_bounds__(256) void k_rows_elements(const RowArgs a) {
   const int t = blockIdx.x, tid = threadIdx.x;
   const int64_t V = a.tok.V;
   const Tin* row = static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld;
-  const bool staged = a.chunk != 0;
+  const bool staged = !HELD && a.chunk != 0;
+  Tin z[U];
+  if constexpr (HELD) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (tid + u * NT < V) z[u] = row[tid + u * NT];
+  }
   const TokenIn in = token_load(a.tok, t);
   // f(column, logit) for the thread's columns in order
   auto sweep = [&](auto from_lds, auto f) {
-    for (int64_t base = tid; base < V; base += NT * U) {
-      Tin z[U];
+    for (int64_t base = tid; base < (HELD ? NT : V); base += NT * U) {
+      if constexpr (!HELD) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t v = base + u * NT;
-        if (v < V) z[u] = from_lds ? stage[v] : row[v];
+        for (int u = 0; u < U; ++u) {
+          const int64_t v = base + u * NT;
+          if (v < V) z[u] = from_lds ? stage[v] : row[v];
+        }
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -799,6 +808,18 @@ static bool records_without_dlogits(grpo_dtype dt, int64_t T, int64_t V, int n_c
 constexpr int kPipeMinNV = 11, kPipeMaxNV = 23;  // at most 15 register vectors and 9 LDS vectors per thread
 constexpr int64_t kPipeMaxT = (int64_t)1 << 30;  // t + (gridDim.x - 1) * chunk + 1 stays far below 2^31
 
+// Rows of up to kHeldElements elements a thread stay in registers, with no more in flight than the row has: a row of 101
+// or 1,003 staged in LDS with 16 in flight a thread took 64 and 74 us (fp32, 20,000 rows), longer than element by
+// element from memory.  Held / staged beyond, 16 a thread: bf16 4,093 / 4,097 columns 154 / 126 us, fp32 137 / 146.
+constexpr int kHeldElements = 8;
+template <typename Tin>
+static RowKernel element_kernel(int64_t V) {
+  if (V <= 256) return k_rows_elements<Tin, 1, true>;
+  if (V <= 1024) return k_rows_elements<Tin, 4, true>;
+  if (V <= 256 * kHeldElements) return k_rows_elements<Tin, kHeldElements, true>;
+  return k_rows_elements<Tin, 16, false>;
+}
+
 struct Launch {
   RowKernel k;
   int nt;
@@ -851,8 +872,8 @@ static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, c
   // staged in LDS where two workgroups fit a CU: alone on its CU, 256 threads took 0.96 ms at fp32 10,000 x 32,003
   // against 0.80 with every sweep from memory
   const int64_t bytes = V * (16 / epv);
-  const bool staged = bytes <= 79 * 1024;
-  return Launch{dt == GRPO_BF16 ? k_rows_elements<uint16_t> : k_rows_elements<float>, 256, (unsigned)T, staged, 0, 1,
+  const bool staged = V > 256 * kHeldElements && bytes <= 79 * 1024;
+  return Launch{dt == GRPO_BF16 ? element_kernel<uint16_t>(V) : element_kernel<float>(V), 256, (unsigned)T, staged, 0, 1,
                 staged ? (unsigned)bytes : 0u};
 }
 

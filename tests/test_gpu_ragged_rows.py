@@ -186,3 +186,18 @@ def test_fp32_rows_of_more_than_8_mb():
     d = got[0][0][T - 1].double()
     g = d[act[T - 1].item()] / p[act[T - 1].item()]
     assert (d - g * p).abs().max().item() <= 1e-5 * d.abs().max().item()
+
+
+# the element kernel's rows of 1, 4 and 8 elements a thread held in registers and the first beyond; the log-probs' rows of
+# one wave (8 KB) and the first beyond
+SHORT = [(255, 255, "f32"), (256, 257, "bf16"), (257, 257, "f32"), (1023, 1023, "bf16"), (1024, 1025, "f32"),
+         (1025, 1025, "f32"), (2047, 2047, "f32"), (2048, 2049, "f32"), (2049, 2049, "f32"), (2049, 2049, "bf16"),
+         (4096, 4097, "bf16"), (4097, 4097, "bf16")]
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("V,ld,dtype", SHORT)
+def test_short_rows(V, ld, dtype, offset):
+    test_loss_rows(V, ld, dtype, offset)
+    test_logp_and_records(V, ld, dtype, offset)
+    test_logits_masked_with_the_lowest_value(V, ld, dtype, None, 100)
