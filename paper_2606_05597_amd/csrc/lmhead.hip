@@ -1544,10 +1544,13 @@ extern "C" int fused_lmhead_token_logp(const void* hidden, const void* w_lm, int
   float2* part = reinterpret_cast<float2*>(w + L.part);
   float* part_t = reinterpret_cast<float*>(w + L.part_t);
   const int n_tiles = (int)((V + TILE - 1) / TILE);
-  // W^T packed where its 32-column blocks are whole, so that it takes no more room than as a matrix, and K is long:
-  // matrix / packed, 4,001 x 3,584 x 151,936 4.21 / 4.09 ms, 12,000 rows 11.92 / 11.49, 4,001 x 1,024 x 32,000 0.328 /
-  // 0.331
-  const bool packed = V % 32 == 0 && H >= 2048;
+  // W^T packed where its 32-column blocks are whole, so that it takes no more room than as a matrix, and K is long.
+  // Few rows gain by the packing, which is faster than the transposition; many by the core, but only where W^T (V rows)
+  // is long.  Matrix / packed in us: H = 2,048, V = 2,048 64 rows 60 / 58, 4,000 72 / 79; V = 8,000 65 / 64, 150 / 160;
+  // V = 32,000 95 / 94, 544 / 547; H = 4,096, V = 8,000 110 / 106, 263 / 285; V = 24,000 300 rows 191 / 173, 4,000 739 /
+  // 750; V = 64,000 411 / 344, 2,011 / 1,941; H = 3,584, V = 151,936 4,000 rows 4,246 / 4,171.  H = 1,024, V = 32,000
+  // 58 / 59, 327 / 331.
+  const bool packed = V % 32 == 0 && H >= 2048 && (T <= 384 || V >= 32000);
   lm_wt(static_cast<const uint16_t*>(w_lm), H, V, packed, WT, s);
   PartialArgs pa{};
   pa.g = GemmArgs{h16, WT, H, H, (int)T, (int)V, (int)H};

@@ -109,3 +109,20 @@ def test_fused_logp_invalid_action_and_empty():
     e = {"hidden": b["hidden"][:0], "W": b["W"], "actions": b["actions"][:0]}
     logp, ent, flags = run(e)
     assert logp.numel() == 0 and ent.numel() == 0 and flags == 0
+
+
+@pytest.mark.parametrize("V", [320, 328, 32000])
+@pytest.mark.parametrize("T", [384, 385])
+def test_fused_logp_both_layouts_of_w(T, V):
+    # long K: W^T packed for up to 384 rows or from 32,000 columns on, where its 32-column blocks are whole
+    H = 2048
+    g = torch.Generator("cuda").manual_seed(57)
+    h = torch.randn((T, H), generator=g, device="cuda").to(torch.bfloat16)
+    W = (torch.randn((H, V), generator=g, device="cuda") / H ** 0.5).to(torch.bfloat16)
+    act = torch.randint(0, V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    logp, ent, flags = run({"hidden": h, "W": W, "actions": act})
+    assert flags == 0
+    l = torch.log_softmax(h.double() @ W.double(), 1)
+    assert (logp.double() - l.gather(1, act.long()[:, None])[:, 0]).abs().max().item() <= LOGP_ATOL
+    want = -(l.exp() * l).sum(1)
+    assert ((ent.double() - want).abs() <= ENT_ATOL + ENT_RTOL * want.abs()).all()
