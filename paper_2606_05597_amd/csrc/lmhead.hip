@@ -1153,9 +1153,16 @@ static void lm_pass2(const Pass2& q, hipStream_t s) {
   }
 }
 
-// The token-blocked schedule's workspace: W^T and W in the fragment-packed layout (the B operands of the forward
-// and dhidden products), h^T, the fp32 logits of two blocks (the next block's forward product runs while the D
-// pass reads the previous block's when a second stream is given), the D and the packed D^T of one block.
+// Whether packing W for the dhidden product can pay: it costs 0.39 ms at 3,584 x 151,936 whatever T is, and the packed
+// core gains 2 to 5% of the dhidden tiles, 15 to 20% where W's rows are not multiples of 128 bytes (its loads then
+// straddle the lines); both scale with W's size.  The whole call without / with it: V = 151,936 (H = 3,584) T = 4,096
+// 12.25 / 12.41 ms, 8,192 24.4 / 24.3, 16,384 47.9 / 47.7; V = 50,000 (H = 2,048) T = 4,096 2.65 / 2.52 ms, 5,000 3.19 /
+// 3.09, 8,192 4.97 / 4.78; V = 8,008 (H = 4,096) 2,304 0.552 / 0.582, 4,096 0.799 / 0.800.
+static bool pack_w_pays(int64_t T, int64_t V) { return T >= (V % 64 == 0 ? 8192 : 4096); }
+
+// The token-blocked schedule's workspace: W^T and, where it may be used, W in the fragment-packed layout (the B operands
+// of the forward and dhidden products), h^T, the fp16 terms of two blocks (the next block's forward product runs while
+// the D pass reads the previous block's when a second stream is given), the D and the packed D^T of one block.
 struct LmBlockWs {
   LossWs loss;
   size_t wt, wp, ht, part, rs, z, d, dt, total;
@@ -1171,7 +1178,7 @@ static LmBlockWs lm_block_ws_layout(int64_t T, int64_t H, int64_t V, int32_t Tb,
   l.ldz = (int64_t)l.n_tiles * TILE;
   size_t o = l.loss.total;
   l.wt = o;   o = align_up(o + (size_t)packed_bytes(V, H));
-  l.wp = o;   o = align_up(o + (size_t)packed_bytes(H, V));
+  l.wp = o;   o = align_up(o + (pack_w_pays(T, V) ? (size_t)packed_bytes(H, V) : 0));
   l.ht = o;   o = align_up(o + sizeof(uint16_t) * (size_t)(H * l.Tp));
   const size_t nbuf = l.Tp > l.Tbp ? 2 : 1;  // the tile partials and terms of two blocks in flight
   l.part = o; o = align_up(o + sizeof(float2) * (size_t)(l.Tbp * l.n_tiles) * nbuf);
@@ -1183,39 +1190,58 @@ static LmBlockWs lm_block_ws_layout(int64_t T, int64_t H, int64_t V, int32_t Tb,
   return l;
 }
 
-// From this many tokens on, W is packed for the dhidden product as well as W^T for the forward one: the pack takes
-// 0.39 ms at 3,584 x 151,936 whatever T is, the packed core gains 2% of the dhidden tiles.  The whole call without /
-// with it at that W: T = 4,096 12.25 / 12.41 ms, 8,192 24.4 / 24.3, 16,384 47.9 / 47.7; both scale with W's size.
-constexpr int64_t kPackWMinT = 8192;
-
 // How a backward launch takes its dhidden tiles: K, the vocabulary, in `splits` ranges of split_k columns.
 struct DhPlan {
   int splits, split_k;
 };
 
+// The time until n tiles of length a and then m >= 1 tiles of length b, dispatched in this order to n_cu CUs as they come
+// free, are done.
+static double dispatch_time(int64_t n, double a, int64_t m, double b, int n_cu) {
+  const int64_t late = n % n_cu, early = n_cu - late;  // `late` CUs come free one tile after the others
+  const double start = (double)(n / n_cu) * a, wait = a / b;
+  const auto up = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
+  if (late == 0) return start + (double)up(m, n_cu) * b;
+  // the last tile ends on one of the early CUs, after k tiles there and k - ceil(wait) on a late one ...
+  int64_t k = up(m, early);
+  if (k > (int64_t)ceil(wait)) k = up(m + late * (int64_t)ceil(wait), n_cu);
+  // ... or on one of the late CUs, after l tiles there and l + floor(wait) on an early one
+  const int64_t l = std::max<int64_t>(1, up(std::max<int64_t>(0, m - early * (int64_t)floor(wait)), n_cu));
+  return start + std::max(a, std::min((double)k * b, a + (double)l * b));
+}
+
 // A dhidden tile walks the whole vocabulary, so a block of few rows has few tiles, each as long as all of the launch
 // should take: at 700 x 3,584 x 151,936 42 tiles of 2,374 slabs kept 42 CUs busy for 3.78 ms while the dW tiles were
-// done in under 1; the whole call took 5.3 ms and takes 2.9 (T = 64: 4.1 and 1.5; 1,500: 6.4 and 5.0; 4,096 and more
+// done in under 1; the whole call took 5.3 ms and takes 2.8 (T = 64: 4.1 and 1.5; 1,500: 6.4 and 4.9; 4,096 and more
 // stay whole: 12.1).  The ranges are chosen for the shortest launch, counted in 64-deep slabs per CU (about 1.6 us
-// each): no shorter than the rounds of dhidden tiles, dispatched first, nor than all tiles spread evenly and one dW
-// tile more; a quarter of the time that the last round leaves CUs without a dhidden tile is taken as lost (the dW
-// tiles fill it, but the streams of D and W then run below the memory's rate); a tile's store counts 8 slabs, and the
-// partials (scratch_floats at most) are written, read and summed in a launch of their own.
-static DhPlan dh_plan(int64_t rows, int64_t H, int64_t V, int accumulate, int64_t scratch_floats, int n_cu) {
+// each): dhidden tiles dispatched first, then the dW tiles, a tile's store counting 2 slabs, and a twentieth of the time
+// that the last round leaves CUs without a dhidden tile (the dW tiles fill it, but the streams of D and W then run below
+// the memory's rate); the partials (scratch_floats at most) are written, read and summed in a launch of their own.  A
+// slab of W as it lies counts 1.16 where its rows are not multiples of 128 bytes, of W packed (whole tiles alone;
+// pack_slabs, the packing's share, or < 0 for no packed copy) 0.95.  Of 230 launches timed (512 to 8,192 rows, H 512 to
+// 4,096, V 8,000 to 151,936, dW stored and accumulated) with one to 15 ranges, the choice is within 0.5% of the fastest
+// on average and 4.5% at worst.  With the launch's length taken as an even share of all tiles it was up to 19% slower
+// (3,000 x 1,024 x 8,000), and up to 7% slower than whole packed tiles where W's rows are not multiples of 128 bytes.
+static DhPlan dh_plan(int64_t rows, int64_t H, int64_t V, int accumulate, int64_t scratch_floats, double pack_slabs,
+                      int n_cu) {
   const int64_t nk = (V + 63) / 64, kb = (rows + 63) / 64;
   const int64_t n_dh = (rows + TILE - 1) / TILE * ((H + TILE - 1) / TILE);
   const int64_t n_dw = (V + TILE - 1) / TILE * ((H + TILE - 1) / TILE);
-  const double store = 8.0, dw = (double)kb + store * (accumulate ? 2 : 1);
+  const double store = 2.0, dw = (double)kb + store * (accumulate ? 2 : 1);
+  const double slab = V % 64 == 0 ? 1.0 : 1.16, packed_slab = 0.95;
   DhPlan best{1, (int)(nk * 64)};
   double best_t = 0.0;
   for (int64_t s = 1; s <= 16 && s <= nk; ++s) {
     const int64_t per = (nk + s - 1) / s, ranges = (nk + per - 1) / per;
     if (ranges < s) continue;
     if (s > 1 && s * rows * H > scratch_floats) break;
+    const bool packed = s == 1 && pack_slabs >= 0.0;
     const int64_t n = n_dh * s;
-    const double dh = (double)per + store, rounds = (double)((n + n_cu - 1) / n_cu) * dh, share = (double)n * dh / n_cu;
-    double t = std::max(rounds, share + (double)n_dw * dw / n_cu + dw) + 0.25 * (rounds - share);
+    const double dh = (double)per * (packed ? packed_slab : slab) + store;
+    double t = dispatch_time(n, dh, n_dw, dw, n_cu) +
+               0.05 * ((double)((n + n_cu - 1) / n_cu) - (double)n / n_cu) * dh;
     if (s > 1) t += 6.0 + (double)(s * rows * H) * 8.0 / 8e6;
+    if (packed) t += pack_slabs;
     if (s == 1 || t < best_t) {
       best = DhPlan{(int)s, (int)(per * 64)};
       best_t = t;
@@ -1380,17 +1406,22 @@ extern "C" int fused_lmhead_grpo_blocked(const void* hidden, const void* w_lm, i
   lm_transpose(W16, h16, T, H, V, Tp, nullptr, hT, s);
   hipLaunchKernelGGL(k_pack_t, dim3((unsigned)((V + 63) / 64), (unsigned)((H + 63) / 64)), dim3(256), 0, s, W16, V,
                      (int)H, (int)V, WT);
-  const bool pack_w = T >= kPackWMinT;
+  const int n_cu = stream_cu_count(s);  // of the stream's device, which need not be the current one
+  if (n_cu < 1) return GRPO_ERR_HIP;
+  const int n_blocks = (int)((T + L.Tbp - 1) / L.Tbp);
+  // the partials of a split go where the block's terms were, which its D pass has read
+  const int64_t scratch = L.Tbp * L.ldz / 2;
+  // W is packed if a whole block's launch uses it, which has its share of the packing (0.39 ms at 3,584 x 151,936)
+  const double pack_slabs = 4.5e-7 * (double)(H * V) / n_blocks;
+  const bool pack_w = pack_w_pays(T, V) && dh_plan(std::min(T, L.Tbp), H, V, n_blocks > 1 || accumulate_dw, scratch,
+                                                   pack_slabs, n_cu).splits == 1;
   if (pack_w)
     hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)(packed_kb_count(V) / 4), (unsigned)((H + 31) / 32)), dim3(256), 0,
                        s, W16, V, (int)H, (int)V, WP);
-  const int n_cu = stream_cu_count(s);  // of the stream's device, which need not be the current one
-  if (n_cu < 1) return GRPO_ERR_HIP;
   if (hipGetLastError() != hipSuccess) return GRPO_ERR_HIP;
   const bool timed = aux && aux->hot_begin && aux->hot_end;
   if (timed && hipEventRecord(aux->hot_begin, s) != hipSuccess) return GRPO_ERR_HIP;
   const TokenArgs tok = make_token_args(V, actions, behave_logp, prox_logp, adv, p, w, L.loss, aux);
-  const int n_blocks = (int)((T + L.Tbp - 1) / L.Tbp);
   auto rows_of = [&](int b) { return (int)(T - (int64_t)b * L.Tbp < L.Tbp ? T - (int64_t)b * L.Tbp : L.Tbp); };
   auto rows64 = [](int rows) { return (rows + 63) / 64 * 64; };  // a block's rows of D and D^T, zeros past its own
   auto e_of = [&](int b) { return e16 + (size_t)(b & 1) * (size_t)(L.Tbp * L.ldz); };
@@ -1432,8 +1463,7 @@ extern "C" int fused_lmhead_grpo_blocked(const void* hidden, const void* w_lm, i
     const int64_t t0 = (int64_t)b * L.Tbp;
     const int rows = rows_of(b);
     const int acc_dw = (b > 0 || accumulate_dw) ? 1 : 0;
-    // the partials of a split go where the block's terms were, which its D pass has read
-    const DhPlan plan = dh_plan(rows, H, V, acc_dw, L.Tbp * L.ldz / 2, n_cu);
+    const DhPlan plan = dh_plan(rows, H, V, acc_dw, scratch, pack_w ? 0.0 : -1.0, n_cu);
     const bool packed = pack_w && plan.splits == 1;
     BackwardArgs ba;
     ba.dh.g = packed ? GemmArgs{D, WP, L.ldz, 0, rows, (int)H, (int)V} : GemmArgs{D, W16, L.ldz, V, rows, (int)H, (int)V};
@@ -1685,7 +1715,7 @@ extern "C" int fused_lmhead_grpo_vocab_shard(const void* hidden, const void* w_s
     // the partials of a split go where W^T would be
     const int n_cu = stream_cu_count(s);
     if (n_cu < 1) return GRPO_ERR_HIP;
-    const DhPlan plan = dh_plan(T, H, V_shard, accumulate_dw, V_shard * H / 2, n_cu);
+    const DhPlan plan = dh_plan(T, H, V_shard, accumulate_dw, V_shard * H / 2, -1.0, n_cu);
     BackwardArgs ba;
     ba.dh.g = GemmArgs{D, W16, Vsp, V_shard, (int)T, (int)H, (int)V_shard};
     ba.dh.acc = plan.splits > 1 ? reinterpret_cast<float*>(WT) : dhidden_partial;

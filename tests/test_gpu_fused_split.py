@@ -81,3 +81,10 @@ def test_forward_only_packed(T, H, V):
         assert np.abs(logp.double().cpu().numpy() - ref.token_logp).max() <= 2e-4
         if entropy:
             assert (np.abs(ent.double().cpu().numpy() - ref.token_entropy) <= 4e-4 + 2e-5 * np.abs(ref.token_entropy)).all()
+
+
+@pytest.mark.parametrize("T,H,V,block,streams", [(4095, 64, 600, 8192, 1), (4096, 64, 600, 8192, 1),
+                                                 (4099, 320, 1032, 2048, 1), (4099, 320, 1032, 2048, 2)])
+def test_packed_w_where_its_rows_are_not_whole_lines(T, H, V, block, streams):
+    # whole dhidden tiles on the packed W from 4,096 rows on where V is not a multiple of 64, a short last block among them
+    test_split_dhidden(T, H, V, block, streams)
