@@ -51,6 +51,12 @@ def _watched():
             or torch.compiler.is_compiling())
 
 
+# Elements of dW from which its scale and its rounding are one pass: 8 bytes less to move per element, 6 us at 5.3 TB/s
+# here, what a call of the library costs the autograd engine's thread more than the two torch operations do.  A backward
+# of 64 x 512 weights took 85 us of host time with the one pass and 80 with the two operations.
+_ONE_PASS_MIN = 1 << 22
+
+
 def _scaled_to_bf16(t, grad_output):
     """(t * grad_output in fp32) rounded to bf16, in one pass over t where nothing has to see the two operations
     (_watched, _plain), a contiguous t as the library wrote it."""
@@ -119,5 +125,8 @@ class FusedLmHeadGrpoLoss(torch.autograd.Function):
         if ctx.needs_input_grad[0]:
             (dh,) = _apply_upstream(ctx.upstream, (dhidden,), grad_output)
         if ctx.needs_input_grad[1]:  # w_lm is bf16 (the entry points take nothing else)
-            dW = dw.to(torch.bfloat16) if ctx.upstream == "unit" else _scaled_to_bf16(dw, grad_output)
+            if ctx.upstream == "scale" and dw.numel() >= _ONE_PASS_MIN:
+                dW = _scaled_to_bf16(dw, grad_output)
+            else:
+                dW = _apply_upstream(ctx.upstream, (dw,), grad_output)[0].to(torch.bfloat16)
         return dh, dW, None, None, None, None, None, None, None

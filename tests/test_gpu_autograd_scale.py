@@ -92,3 +92,24 @@ def test_an_upstream_gradient_without_memory():
     zero = torch._efficientzerotensor((), device="cuda")  # known to be zero: no storage behind it
     with torch.no_grad():
         assert torch.equal(_scaled_to_bf16(x, zero) + 0, torch.zeros_like(x, dtype=torch.bfloat16))
+
+
+@pytest.mark.parametrize("V", [65528, 65536])
+def test_wrapper_scales_small_and_large_dw(V):
+    import paper_2606_05597_amd as grpo
+    T, H = 40, 64  # H V on both sides of the one pass's 2^22 elements
+    gen = torch.Generator("cuda").manual_seed(4)
+    h = torch.randn((T, H), device="cuda", generator=gen).to(torch.bfloat16)
+    W = (torch.randn((H, V), device="cuda", generator=gen) / 8).to(torch.bfloat16)
+    act = torch.randint(0, V, (T,), device="cuda", generator=gen, dtype=torch.int32)
+    behave = torch.full((T,), -11.0, device="cuda")
+    adv = torch.tensor([1.0, -1.0], device="cuda")
+    sto = torch.tensor([0, 10, 25, T], dtype=torch.int32, device="cuda")
+    tso = torch.tensor([0, 1, 3], dtype=torch.int32, device="cuda")
+    _, dh, dw = grpo.fused_lmhead_grpo_blocked(h, W, act, behave, adv, sto, tso, 2)
+    hp, Wp = h.clone().requires_grad_(True), W.clone().requires_grad_(True)
+    loss = grpo.FusedLmHeadGrpoLoss.apply(hp, Wp, act, behave, adv, sto, tso, 2, {"schedule": "blocked"})
+    (loss * 0.3).backward()
+    g = torch.tensor(0.3, dtype=torch.float64, device="cuda")
+    assert torch.equal(Wp.grad, torch.mul(dw, g.float()).to(torch.bfloat16))
+    assert torch.equal(hp.grad, torch.mul(dh, g.to(torch.bfloat16)))
