@@ -12,7 +12,7 @@ namespace grpo {
 struct WsHeader {
   int32_t flags;      // GRPO_FLAG_* of this call (set by the segment pass, OR-ed by the row pass)
   uint32_t done;      // reduction workgroups finished (last-block pattern)
-  int64_t counts[4];  // [0]: eps-clip cut, dual-clip cut; [1]: ratio outside the clip range, valid tokens (each pair
+  int64_t counts[2];  // [0]: eps-clip cut, dual-clip cut; [1]: ratio outside the clip range, valid tokens (each pair
                       // the low and high 32 bits)
 };
 

@@ -45,10 +45,10 @@ struct RowArgs {
   void* dlogits;  // nullable: forward only
   int64_t ld;     // row stride in elements
   int T;
-  int chunk;      // k_rows_pipe: consecutive rows a workgroup takes at a time (>= 1) in rows [0, r0); k_rows_elements:
-                  // whether the dynamic LDS holds a row
+  int chunk;      // k_rows_pipe: consecutive rows a workgroup takes at a time (>= 1) in rows [0, r0)
   int r0;         // k_rows_pipe: a multiple of chunk * gridDim.x
   int chunk2;     // k_rows_pipe: rows [r0, T) go chunk2 at a time, one chunk per workgroup (>= 1)
+  bool staged;    // k_rows_elements: the dynamic LDS holds a row
   TokenArgs tok;
 };
 
@@ -692,7 +692,7 @@ __global__ __launch_bounds__(256) void k_rows_elements(const RowArgs a) {
   const int t = blockIdx.x, tid = threadIdx.x;
   const int64_t V = a.tok.V;
   const Tin* row = static_cast<const Tin*>(a.logits) + (int64_t)t * a.ld;
-  const bool staged = !HELD && a.chunk != 0;
+  const bool staged = !HELD && a.staged;
   Tin z[U];
   if constexpr (HELD) {
 #pragma unroll
@@ -750,7 +750,7 @@ typedef void (*RowKernel)(const RowArgs);
 
 struct Variant {
   int nt, nv;
-  RowKernel bf16[2], f32;  // bf16: whole aligned vectors, ragged
+  RowKernel bf16[2], f32;  // bf16: whole aligned vectors, ragged; none where the persistent kernels come first
 };
 
 #define GRPO_VARIANT(NT, NV)                                                                     \
@@ -758,6 +758,8 @@ struct Variant {
     NT, NV, {k_rows_resident<uint16_t, NT, NV, false>, k_rows_resident<uint16_t, NT, NV, true>}, \
         k_rows_resident<float, NT, NV, false>                                                    \
   }
+#define GRPO_VARIANT_F32(NT, NV) \
+  { NT, NV, {nullptr, nullptr}, k_rows_resident<float, NT, NV, false> }
 
 // Searched in order; the first that holds the row is used.  Rows of 3,073 to 4,096 vectors (a bf16 vocabulary of
 // 32,000 among them) take 1024 threads x 4 vectors: 6% faster there than 256 x 16 (0.707 against 0.752 ms at
@@ -766,7 +768,7 @@ static const Variant kVariants[] = {
     GRPO_VARIANT(64, 1),    GRPO_VARIANT(64, 2),    GRPO_VARIANT(64, 4),    GRPO_VARIANT(64, 8),
     GRPO_VARIANT(256, 4),   GRPO_VARIANT(256, 8),   GRPO_VARIANT(256, 12),  GRPO_VARIANT(1024, 4),
     GRPO_VARIANT(256, 20),  GRPO_VARIANT(256, 24),  GRPO_VARIANT(1024, 8),  GRPO_VARIANT(1024, 12),
-    GRPO_VARIANT(1024, 16), GRPO_VARIANT(1024, 19),
+    GRPO_VARIANT_F32(1024, 16), GRPO_VARIANT_F32(1024, 19),
 };  // 1024 threads x 19 vectors is the largest that does not spill
 
 // The persistent kernels for long bf16 rows, one per NV = ceil(V/8/1024) so
@@ -825,7 +827,7 @@ struct Launch {
   int nt;
   unsigned grid;
   int chunk = 1, r0 = 0, chunk2 = 1;
-  unsigned lds = 0;    // dynamic LDS bytes
+  unsigned lds = 0;    // dynamic LDS bytes: k_rows_elements with its rows staged
   bool twice = false;  // without k: k_rows_twice
 };
 
@@ -863,7 +865,8 @@ static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, c
       return Launch{k, 1024, (unsigned)g, (int)chunk, (int)r0, (int)chunk2};
     }
     for (const Variant& v : kVariants) {
-      if ((int64_t)v.nt * v.nv >= nvec) return Launch{dt == GRPO_BF16 ? v.bf16[rag] : v.f32, v.nt, (unsigned)T};
+      const RowKernel fits = dt == GRPO_BF16 ? v.bf16[rag] : v.f32;
+      if (fits && (int64_t)v.nt * v.nv >= nvec) return Launch{fits, v.nt, (unsigned)T};
     }
     Launch l{nullptr, 0, 0};  // two passes, or fp32 rows in one
     l.twice = dt == GRPO_F32 && rows_twice(T, V, n_cu) && (dlogits || !records_without_dlogits(dt, T, V, n_cu));
@@ -873,8 +876,9 @@ static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, c
   // against 0.80 with every sweep from memory
   const int64_t bytes = V * (16 / epv);
   const bool staged = V > 256 * kHeldElements && bytes <= 79 * 1024;
-  return Launch{dt == GRPO_BF16 ? element_kernel<uint16_t>(V) : element_kernel<float>(V), 256, (unsigned)T, staged, 0, 1,
-                staged ? (unsigned)bytes : 0u};
+  Launch l{dt == GRPO_BF16 ? element_kernel<uint16_t>(V) : element_kernel<float>(V), 256, (unsigned)T};
+  if (staged) l.lds = (unsigned)bytes;
+  return l;
 }
 
 }  // namespace grpo
@@ -926,6 +930,7 @@ extern "C" int grpo_loss_fwd_bwd(const void* logits, int32_t dtype, int64_t T, i
     a.chunk = k.chunk;
     a.r0 = k.r0;
     a.chunk2 = k.chunk2;
+    a.staged = k.lds > 0;
     const bool timed = aux && aux->hot_begin && aux->hot_end;
     if (timed && hipEventRecord(aux->hot_begin, s) != hipSuccess) return GRPO_ERR_HIP;
     if (k.k) {
