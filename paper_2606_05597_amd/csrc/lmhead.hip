@@ -1709,7 +1709,7 @@ extern "C" int fused_lmhead_grpo_vocab_shard(const void* hidden, const void* w_s
   if (hipGetLastError() != hipSuccess) return GRPO_ERR_HIP;
   if (logits_in) {
     // D, D^T of the whole shard from its stored logits, then dW (K = Tp) and the fp32 partial dhidden (K = V_shard)
-    // in one launch, the long dW tiles first
+    // in one launch
     const BlockDArgs da{logits_in, nullptr, nullptr, 0, rs, D, DT, Vsp, (int)V_shard, Tp};
     hipLaunchKernelGGL(k_lm_block_d, dim3(block_d_grid(Tp, Vsp, 0)), dim3(256), 0, s, da);
     // the partials of a split go where W^T would be

@@ -195,8 +195,9 @@ struct TwiceArgs {
 // One workgroup per row of whole aligned vectors: the row's sum as k_logp_vec forms it for a record (the same terms in
 // the same order, so that the results are those of the two launches to the bit), the token epilogue, then dlogits.  A
 // thread's first HR vectors stay in registers and the next HL in LDS (rows have more than that); the rest is read a
-// second time, backwards, the end of the row from the L2 and the most of it from the memory-side cache: at two
-// workgroups per CU, which the registers and the LDS are sized for, the rows in flight are less than its 256 MB.
+// second time, backwards, the end of the row from the L2 and, at two workgroups per CU, which the registers and the LDS
+// are sized for, as much more from the memory-side cache as its 256 MB hold of the rows in flight: 512 rows of up to
+// 0.5 MB (131,072 columns) beside what is held, less of longer ones.
 // HBM-bound.  fp32 loss and dlogits, in two launches / here: 6,000 x 151,936 2.01 / 1.48 ms (4.9 TB/s of the row read and
 // written once), 8,000 x 100,000 1.68 / 1.22, 3,000 x 262,144 1.62 / 1.32, 800 x 1,000,000 1.89 / 1.78, 64 x 151,936
 // 0.078 / 0.042; with nothing held 1.60 at 151,936, with more workgroups per CU 1.66 to 2.0.

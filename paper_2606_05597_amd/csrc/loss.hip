@@ -17,11 +17,12 @@
 //  k_rows_stream    bf16 rows that one CU cannot hold (beyond 188,416 columns), up
 //                   to 4 MiB: persistent, most of the row held, the rest read a
 //                   second time from the caches.
-//  k_rows_twice     (logp.hip) fp32 rows beyond 77,824 columns: one workgroup per
-//                   row, part of it held, the rest read a second time.
-//  two passes       longer rows: each row reduced to a record (logp.hip), then
-//                   the record turned into the token epilogue and the row's
-//                   dlogits (vocab.hip); the row is read twice.
+//  k_rows_twice     (logp.hip) fp32 rows beyond 77,824 columns (rows_twice): one
+//                   workgroup per row, part of it held, the rest read a second time.
+//  two passes       longer rows, and long rows without dlogits: each row reduced
+//                   to a record (logp.hip), then the record turned into the token
+//                   epilogue and the row's dlogits (vocab.hip), which reads the
+//                   row again.
 //  k_rows_elements  fp32 rows that are not whole 16-byte vectors, and rows whose
 //                   dlogits lie at another distance from a 16-byte boundary than
 //                   their logits: element loads.
@@ -402,8 +403,9 @@ __global__ __launch_bounds__(1024) void k_rows_pipe(const RowArgs a) {
 // As k_rows_pipe (one workgroup of 1024 threads per CU, 16-byte vectors j * 1024 + tid), with the row in three parts:
 // vectors 0 .. NP-1 in LDS, the next NR in registers, and the rest streamed, U at a time, through one more set of
 // registers.  The streamed part is read twice: forwards for (max, sum exp), then, beginning with the last U vectors,
-// which are still there, backwards for dlogits.  HBM-bound: the second read finds its vectors in the memory-side
-// cache, since all CUs together have read less than its 256 MB in between (kStreamMaxRow).
+// which are still there, backwards for dlogits.  HBM-bound.  What the second read finds in the memory-side cache depends
+// on how much all CUs together have read in between: up to rows of about 1 MB (256 CUs, 256 MB) most of it, of longer
+// rows their ends; the third of a MB per row that the CU holds is saved in any case.
 // A row fills the first two parts (at least NP + NR vectors and one element more per thread).
 // Every load and store is issued whatever the row's length (stores past it are dropped by the range check of the row's
 // descriptor), so that the wait for the LDS part counts the same operations on every row.
@@ -786,7 +788,8 @@ static const RowKernel kPipe[][2] = {
 // 2.56 / 1.80.  13 + 5 and 14 + 6 register vectors, which spill, are 1 to 3% slower, a first read past the caches 11%.
 static const RowKernel kStreamRows[2] = {k_rows_stream<uint16_t, 9, 12, 4, false>,
                                          k_rows_stream<uint16_t, 9, 12, 4, true>};
-// Rows of up to 4 MiB, beyond which the second read misses more and more (fp32 rows of 4 MB gained 6%).
+// Rows of up to 4 MiB, where the second read misses most of a row and the gain runs out: bf16 in two passes / here, 2,000 x
+// 1,048,576 2.23 / 1.90 ms, 1,000 x 2,097,152 2.26 / 2.12, 700 1.56 / 1.48.
 constexpr int64_t kStreamMaxRow = (int64_t)1 << 22;
 // k_rows_twice: rows addressed with 32-bit offsets, of up to 8 MB, or longer ones while there are too few to fill the
 // chip.  Loss and dlogits in two passes / here, ms: 8 MB a row, 600 rows 2.64 / 2.60, 2,100 9.40 / 9.48; 16 MB, 300 rows
@@ -834,9 +837,9 @@ struct Launch {
 static Launch pick_row_kernel(grpo_dtype dt, int64_t T, int64_t V, int64_t ld, const void* logits,
                               const void* dlogits, hipStream_t s) {
   const int epv = (dt == GRPO_BF16) ? 8 : 4;
-  // fp32 rows that are not whole aligned vectors keep the element kernel's column classes: the vector kernels' other
-  // order of fp32 sums, no less exact, moves the small dlogits of a near-certain token by more (to 5e-4 of the root mean
-  // square) than callers that compare in 32 bits allow
+  // fp32 rows that are not whole aligned vectors keep the element kernel and with it the order of their fp32 sums (column
+  // classes modulo 256).  The ragged vector kernels' order is no less exact, but it moves the small dlogits of a
+  // near-certain token by up to 5e-4 of the root mean square; nothing here reads such rows by vectors in the old order.
   RowForm form = row_form(logits, dlogits, V, ld, 16 / epv);
   if (dt == GRPO_F32 && form == RowForm::kRagged) form = RowForm::kElements;
   const int rag = form == RowForm::kRagged;

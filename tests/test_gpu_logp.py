@@ -6,7 +6,7 @@ Gates (fp32 arithmetic over V terms, sums in fp32 per thread and fp64 across the
     T = sum e^(z - m)(z - m), each accumulated in fp32 over about V/256 terms per thread, so each carries a
     relative error of order 1e-6; both terms are non-negative and at most log V + |H| in size.
 Sizes: the tiny and 32k workloads in full, the 151,936-vocabulary workloads at full size in the benchmark's
-launch configuration on sampled rows, and the edge cases (generic kernel, padded stride, invalid actions,
+launch configuration on sampled rows, and the edge cases (odd vocabularies, padded stride, invalid actions,
 constant and peaked rows, the empty batch).
 """
 import math

@@ -231,7 +231,7 @@ def _sampled_dlogits(b, dl, rows, oi, A64, norm, gs, scaled, what):
 
 @pytest.mark.parametrize("norm", NORMS)
 def test_v32k_parity_full(norm):
-    # the register-resident kernel (256 threads x 16 vectors per row); every row's dlogits against the oracle's,
+    # the register-resident kernel (1,024 threads x 4 vectors per row); every row's dlogits against the oracle's,
     # at grad_scale 1 (absolute 2e-3) and rerun at grad_scale = 1/max|g_t| (the scaled bf16 gate)
     b = make_batch("v32k", "cuda")
     cfg = b["cfg"]
@@ -343,10 +343,10 @@ def _edge_batch(V, dtype="bf16", n_groups=2, G=4, ld=None, seed=5, max_tok=6):
                                      (184320, "bf16"), (200000, "bf16"), (262144, "bf16"), (77824, "f32"),
                                      (100000, "f32"), (151936, "f32")])
 def test_ragged_vocab_and_kernel_variants(V, dtype):
-    # odd V uses the generic row kernel; bf16 rows of 56K to 188K take the pipelined kernel (122,880: one LDS
-    # vector per thread; 128,256: two; 151,936: six; 163,840 and 184,320: nine); fp32 rows up to 77,824 the
-    # register-resident one; longer vector rows (bf16 200,000 and 262,144, fp32 100,000 and 151,936) the two
-    # passes (a record per row, then the epilogue and dlogits)
+    # odd bf16 V are split into vectors and edges, odd fp32 V read by elements; bf16 rows of 81,921 to 188,416 take the
+    # pipelined kernel (122,880: one LDS vector per thread; 128,256: two; 151,936: six; 163,840 and 184,320: nine),
+    # longer ones (200,000 and 262,144) the streaming one; fp32 rows up to 77,824 the register-resident one, longer
+    # ones (100,000 and 151,936) the kernel that reads a row twice
     b = _edge_batch(V, dtype)
     _full_parity(b, oracle.NORM_TRAJ_STEPS, 3.0)
 
@@ -376,7 +376,7 @@ def test_pipelined_kernel_row_chunks(V):
 def test_padded_row_stride():
     b = _edge_batch(1000, "bf16", ld=1024)
     _full_parity(b, oracle.NORM_CONST_K, 0.0)
-    b = _edge_batch(1000, "f32", ld=1003)  # odd stride: generic kernel
+    b = _edge_batch(1000, "f32", ld=1003)  # odd stride: element kernel
     _full_parity(b, oracle.NORM_CONST_K, 0.0)
 
 
@@ -435,9 +435,11 @@ def test_malformed_offsets_flagged():
     assert (aux.traj_tok_off.cpu() == -1).all()
 
 
-@pytest.mark.parametrize("V,dtype", [(256, "bf16"), (32000, "bf16"), (151936, "bf16"), (200000, "bf16")])
+@pytest.mark.parametrize("V,dtype", [(256, "bf16"), (32000, "bf16"), (151936, "bf16"), (200000, "bf16"),
+                                     (1003, "f32"), (100000, "f32"), (2097160, "bf16")])
 def test_nonfinite_logit_flagged(V, dtype):
-    # resident kernels (one workgroup per row), the pipelined kernel, two passes
+    # resident kernels (one workgroup per row), the pipelined and the streaming kernel; element kernel, the kernel that
+    # reads a row twice, two passes
     b = _edge_batch(V, dtype)
     b["logits"][2, 5] = float("nan")
     _, A32 = _adv(b)
@@ -465,10 +467,11 @@ def test_masked_logits(V, dtype):
     assert (dl[:, :V][mask] == 0).all()
 
 
-@pytest.mark.parametrize("V,dtype,big", [(4096, "bf16", False), (100000, "f32", False), (151936, "bf16", True)])
+@pytest.mark.parametrize("V,dtype,big", [(4096, "bf16", False), (100000, "f32", False), (151936, "bf16", True),
+                                         (2097160, "bf16", False)])
 def test_forward_only_and_aliasing(V, dtype, big):
-    # one pass (resident), two passes, and the pipelined kernel with several rows per workgroup (each row's
-    # dlogits overwrite it in place while the workgroup's next row is being loaded)
+    # one pass (resident), the kernel that reads a row twice, the pipelined kernel with several rows per workgroup (each
+    # row's dlogits overwrite it in place while the workgroup's next row is being loaded), and two passes
     b = _edge_batch(V, dtype, n_groups=8, G=4, seed=13, max_tok=72) if big else _edge_batch(V, dtype)
     if big:
         assert b["structure"].T >= 4 * torch.cuda.get_device_properties(0).multi_processor_count

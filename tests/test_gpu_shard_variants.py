@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import oracle
+import paper_2606_05597_amd as grpo
 from synth.rollouts import Config, make_batch
 from tests.gpu_parity import LOSS_RTOL, check_dlogits, dl_to_f64, gpu_norm, oracle_inputs, to_np_logits
 from tests.test_gpu_vocab_shard import _adv, run_sharded
@@ -32,3 +33,28 @@ def test_variants(dtype, shards, Vs):
     assert len(set(losses)) == 1
     assert abs(losses[0] - ref.loss) <= LOSS_RTOL * np.abs(ref.token_contrib).sum()
     check_dlogits(dl_to_f64(dl), ref.dlogits, dtype == "bf16", what=f"{shards} x {Vs}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [5, 1001, 6400])
+def test_dlogits_at_another_distance(V, dtype):
+    # element loads and stores, against the vector kernel's dlogits at the logits' own distance from a 16-byte boundary
+    T, dt = 50, torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator("cuda").manual_seed(V)
+    x = torch.randn((T, V), generator=g, device="cuda").to(dt)
+    act = torch.randint(0, V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    behave = torch.log_softmax(x.float(), 1).gather(1, act.long()[:, None])[:, 0].contiguous()
+    sto = torch.tensor([0, 20, 35, T], dtype=torch.int32, device="cuda")
+    tso = torch.tensor([0, 1, 3], dtype=torch.int32, device="cuda")
+    adv = torch.tensor([1.0, -1.0], device="cuda")
+    stats = grpo.grpo_vocab_shard_stats(x, act, 0).view(1, T, -1)
+    out = []
+    for shift in (0, 1):
+        dl = torch.full((T * V + 16,), 7.0, dtype=dt, device="cuda")
+        loss, _ = grpo.grpo_loss_fwd_bwd_vocab_shard(x, stats, 0, V, act, behave, adv, sto, tso, 2, grad_scale=50.0,
+                                                     dlogits=dl[shift:shift + T * V].view(T, V))
+        assert (dl[:shift] == 7).all() and (dl[shift + T * V:] == 7).all()
+        out.append((loss.item(), dl[shift:shift + T * V].double()))
+    assert out[0][0] == out[1][0]
+    rel = 2.0 ** -7 if dtype == "bf16" else 2.0 ** -22  # a value next to a rounding boundary goes either way
+    assert ((out[0][1] - out[1][1]).abs() <= rel * out[0][1].abs()).all()

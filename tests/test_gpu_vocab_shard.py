@@ -7,8 +7,8 @@ loss pass writes its columns of dlogits.  The concatenated dlogits, the loss and
 to the gates of tests/gpu_parity.py against the oracle's whole-row results; the records against the oracle's
 per-shard statistics (max and action logit exact, the sum relative 5e-6: fp32 partial sums over the shard's
 terms, combined in fp64).  Every shard must produce the same loss bits.  Sizes: the tiny workload (fp32) and
-the 32k-vocabulary workload (bf16) in full, with even, uneven and misaligned splits (the misaligned ones take the
-element kernel); the 151,936-vocabulary workload at full size in 8 shards of 18,992 columns, on sampled rows.
+the 32k-vocabulary workload (bf16) in full, with even, uneven and misaligned splits (the misaligned ones are
+split at the 16-byte boundaries); the 151,936-vocabulary workload at full size in 8 shards of 18,992 columns, on sampled rows.
 """
 import numpy as np
 import pytest
@@ -137,7 +137,7 @@ def _shard_parity(b, bounds, norm, c, scaled=True):
 @pytest.mark.parametrize("norm", [oracle.NORM_TRAJ_STEPS, oracle.NORM_CONST_K])
 @pytest.mark.parametrize("c", [0.0, 3.0])
 def test_tiny_sharded_parity(bounds, norm, c):
-    # [0, 3, 517, 1021, 1024]: shards of 3 columns and misaligned starts take the element kernels
+    # [0, 3, 517, 1021, 1024]: shards of 3 columns and misaligned starts are split at the 16-byte boundaries
     _shard_parity(make_batch("tiny", "cuda", with_prox=(c > 0)), bounds, norm, c)
 
 
