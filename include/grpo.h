@@ -71,6 +71,8 @@ typedef enum {
 #define GRPO_FLAG_ACTION 1    /* some a_t outside [0, V): that row adds 0 and gets a zero dlogits row  */
 #define GRPO_FLAG_OFFSETS 2   /* malformed offsets: every dlogits row is zero and the loss is NaN     */
 #define GRPO_FLAG_NONFINITE 4 /* a non-finite log-prob, input log-prob or advantage; values propagate */
+/* Logits masked with -inf, the type's lowest value or any number from -1e8 down carry no probability; a row of given
+ * logits with nothing above -1e8 has none at all and counts as non-finite. */
 
 /* The ragged batch.  Offsets are device int32 arrays.  Valid offsets:
  * step_tok_off[0] = 0, non-decreasing, step_tok_off[n_steps] = T (a step may
@@ -164,8 +166,8 @@ size_t grpo_loss_workspace_bytes(int64_t T, int32_t n_traj);
  *   seg, p       host structs (above)
  *   loss_out     device fp64 [1]   the loss (not multiplied by grad_scale)
  *   dlogits      device [T, ld] of `dt`; columns >= V are not written; NULL =
- *                forward only.  It may alias `logits` (each row is read in
- *                full before any of it is written).
+ *                forward only.  It may be `logits` itself (every element is
+ *                read for the last time before it is written).
  *   aux          host struct of optional outputs, or NULL
  *   ws, ws_bytes device workspace of at least grpo_loss_workspace_bytes(T, n_traj)
  * The loss and traj_loss are reduced in a fixed order (bitwise reproducible).
@@ -235,7 +237,8 @@ int fused_lmhead_grpo(const void* hidden, const void* w_lm, int64_t T, int64_t H
                       float* dw_lm, int32_t accumulate_dw, grpo_aux* aux, void* ws, size_t ws_bytes,
                       hipStream_t s);
 
-/* Bytes of device workspace fused_lmhead_grpo_blocked needs: besides W^T, h^T and the per-row scales, the fp16
+/* Bytes of device workspace fused_lmhead_grpo_blocked needs: besides W^T, W once more (from 8,192 tokens on, or from
+ * 4,096 where V is not a multiple of 64), h^T and the per-row scales, the fp16
  * logit terms and tile partials of two blocks (one when a single block covers T) and one block's D and D^T,
  * about (2 + 2 + 2 + 2) * B * Vp bytes with B = min(token_block, T rounded up to 256) and Vp = V rounded up to
  * 256 (12.7 GB in all at T = 65,536, H = 3,584, V = 151,936, token_block = 8192).  0 for invalid sizes. */
