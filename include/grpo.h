@@ -71,8 +71,9 @@ typedef enum {
 #define GRPO_FLAG_ACTION 1    /* some a_t outside [0, V): that row adds 0 and gets a zero dlogits row  */
 #define GRPO_FLAG_OFFSETS 2   /* malformed offsets: every dlogits row is zero and the loss is NaN     */
 #define GRPO_FLAG_NONFINITE 4 /* a non-finite log-prob, input log-prob or advantage; values propagate */
-/* Logits masked with -inf, the type's lowest value or any number from -1e8 down carry no probability; a row of given
- * logits with nothing above -1e8 has none at all and counts as non-finite. */
+/* Logits masked with -inf, the type's lowest value or any number from -1e8 down carry no probability.  A row of given
+ * logits with nothing above -1e8 has none at all: non-finite, the log-prob of a finite action logit -inf, its dlogits 0
+ * (a row of -inf alone: NaN). */
 
 /* The ragged batch.  Offsets are device int32 arrays.  Valid offsets:
  * step_tok_off[0] = 0, non-decreasing, step_tok_off[n_steps] = T (a step may
@@ -328,7 +329,7 @@ int fused_lmhead_token_logp(const void* hidden, const void* w_lm, int64_t T, int
  *
  * One shard's per-token record, 24 bytes, all fp64 (no rounding between the
  * shard's reduction and the merge):
- *   m    max over the shard's columns of the row (-inf for a row of -inf)
+ *   m    max over the shard's columns of the row (-inf where none is above -1e8)
  *   s    sum over the shard's columns of exp(z - m)
  *   z_a  the action's logit if a_t is one of the shard's columns, else -inf
  * Any split of a row merges back to its log-sum-exp M + log sum_g s_g exp(m_g - M),

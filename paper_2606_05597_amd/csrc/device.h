@@ -19,6 +19,13 @@ struct WsHeader {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr double kLn2 = 0.69314718055994530942;
 
+// The lowest exp shift m of a thread's sum of e^(z - m), so that logits masked with any large negative number add 0 as
+// -inf does.  A term's argument is z log2(e) less the rounded m log2(e): at z = m it is the rounding's error, up to 8 at
+// m = -1e8 but large enough for an infinite term at -1e10 (and m log2(e) itself overflows at the type's lowest value),
+// and a thread whose whole share of the row is masked then made the row's sum NaN; from 16 on, the fp16 terms that a
+// row keeps in LDS overflowed.  A row with nothing above it has the sum 0 and the log-sum-exp -inf.
+constexpr float kShiftMin = -1e8f;
+
 // ---- bf16 <-> fp32 ---------------------------------------------------------
 // A bf16 value is the upper 16 bits of the fp32 with the same value, so the
 // widening is a shift (low element of a dword) or a mask (high element).
@@ -251,6 +258,8 @@ __device__ inline RowScale token_eval(const TokenArgs& a, const TokenIn& in, dou
     rs.act = -1;
     return rs;
   }
+  // a row that is masked throughout (kShiftMin) has no sum: log-prob -inf and no gradient, whatever the mask's value
+  if (lse == -INFINITY && z_a > -INFINITY && z_a <= (double)kShiftMin) lse = INFINITY;
   e.l = z_a - lse;
   const double b = (double)in.b, p = (double)in.p, A = (double)in.A;
   e.o = token_surrogate(e.l, b, p, A, in.w, a.lo, a.hi, a.c, a.grad_scale);
@@ -351,13 +360,6 @@ __device__ __forceinline__ float max3f(float a, float b, float c) {
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
-
-// The lowest exp shift m of a thread's sum of e^(z - m), so that logits masked with any large negative number add 0 as
-// -inf does.  A term's argument is z log2(e) less the rounded m log2(e): at z = m it is the rounding's error, up to 8 at
-// m = -1e8 but large enough for an infinite term at -1e10 (and m log2(e) itself overflows at the type's lowest value),
-// and a thread whose whole share of the row is masked then made the row's sum NaN; from 16 on, the fp16 terms that a
-// row keeps in LDS overflowed.  A row with nothing above it has the sum 0.
-constexpr float kShiftMin = -1e8f;
 
 // Maximum of m and the vector's elements (the exp shift of the row).
 template <typename Tin>

@@ -115,7 +115,8 @@ __device__ __forceinline__ void row_out(const LogpArgs& a, int t, double M, doub
     return;
   }
   const double lse = M + log(S);
-  if (a.logp) a.logp[t] = act_ok ? (float)(za - lse) : 0.f;
+  const bool masked = lse == -INFINITY && za > -INFINITY && za <= (double)kShiftMin;  // throughout, as in token_eval
+  if (a.logp) a.logp[t] = !act_ok ? 0.f : masked ? -INFINITY : (float)(za - lse);
   // Tsum is in log2 units: sum e^(z - M) (z - M) = Tsum / log2(e)
   if (a.entropy) a.entropy[t] = (float)(log(S) - Tsum / ((double)kLog2e * S));
   if (a.flags) {

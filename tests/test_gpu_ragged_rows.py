@@ -201,3 +201,29 @@ def test_short_rows(V, ld, dtype, offset):
     test_loss_rows(V, ld, dtype, offset)
     test_logp_and_records(V, ld, dtype, offset)
     test_logits_masked_with_the_lowest_value(V, ld, dtype, None, 100)
+
+
+@pytest.mark.parametrize("V,dtype", [(1, "f32"), (64, "bf16"), (101, "f32"), (1003, "bf16"), (32000, "bf16"), (32003, "f32"),
+                                     (57353, "bf16"), (77828, "f32"), (151936, "bf16"), (188440, "bf16"), (200003, "bf16"),
+                                     (2097160, "bf16")])
+@pytest.mark.parametrize("mask", [None, -1e9])
+def test_rows_masked_throughout(V, dtype, mask):
+    # every third row holds the mask alone: log-prob -inf, no gradient, the flag; the other rows as without them
+    cfg, st, lg, act, behave, adv = _batch(V, V, dtype, 0)
+    T = len(act)
+    clean = torch.empty_like(lg)
+    _, ref = _loss(cfg, st, lg, act, behave, adv, V, clean, 1.0)
+    lg[::3] = torch.finfo(lg.dtype).min if mask is None else mask
+    rest = torch.arange(T, device="cuda") % 3 != 0
+    for shift in (0, 1):
+        dl = torch.full((T * V + 16,), 7.0, dtype=lg.dtype, device="cuda")[shift:shift + T * V].view(T, V)
+        loss, aux = _loss(cfg, st, lg, act, behave, adv, V, dl, 1.0)
+        assert np.isfinite(loss) and aux.error_flags.item() == grpo.GRPO_FLAG_NONFINITE
+        assert (aux.token_logp[::3] == -np.inf).all() and (dl[::3] == 0).all()
+        assert (aux.token_logp[rest] - ref.token_logp[rest]).abs().max().item() <= LOGP_ATOL
+        if shift == 0:
+            assert torch.equal(dl[rest], clean[rest])
+    _, alone = _loss(cfg, st, lg, act, behave, adv, V, False, 1.0)
+    assert (alone.token_logp[::3] == -np.inf).all() and torch.isfinite(alone.token_logp[rest]).all()
+    logp, _ = grpo.grpo_token_logp(lg, act)
+    assert (logp[::3] == -np.inf).all() and torch.isfinite(logp[rest]).all()
