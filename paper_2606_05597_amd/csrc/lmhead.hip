@@ -699,9 +699,15 @@ __device__ __forceinline__ void lm_dw_tile(const DwArgs& p, int bid, int nblocks
   // Per 32-row block i: with accumulate, all of its old values are loaded first and waited for once, then
   // added and stored (element by element, every load would wait for the memory in turn).  Without it the stores pass
   // the L2 by, which keeps the h^T and D^T panels of the tiles beside: the fused call and its backward at 3,584 x
-  // 151,936 take 3.475 / 3.437 ms with cached / these stores at 700 rows, 2.64 / 2.60 at 300, 2.050 / 2.060 at 64 (the
-  // call alone 1.470 / 1.454), the same at 16,384; 1,024 x 32,000 at 300 rows 0.227 / 0.220.
-  auto store = [&](auto full, auto accumulate) {
+  // 151,936 take 3.475 / 3.437 ms with cached / these stores at 700 rows, 2.64 / 2.60 at 300, 2.054 / 2.068 at 64 (the
+  // call alone 1.470 / 1.454), the same at 16,384; 1,024 x 32,000 at 300 rows 0.227 / 0.220.  Few rows of a dW whose own
+  // rows are not multiples of 64 bytes have the L2 join the lines' parts: the call at 3,584 x 151,944 takes 1.58 / 1.83 ms
+  // at 64 rows, 1.66 / 1.86 at 128, 4,096 x 32,008 0.466 / 0.526 at 64, 4,096 x 8,008 0.245 / 0.254 at 128 and 0.348 /
+  // 0.334 at 700; rows of whole 64 bytes (3,584 x 18,992) 0.293 / 0.285 at 64, 0.357 / 0.328 at 128.
+  const bool cached = p.V % 16 != 0 && p.g.K <= 128;
+  // The marks keep the compiler from joining the two forms' stores, which it takes for the same, into cached ones.
+  auto store = [&](auto full, auto accumulate, auto through_l2) {
+    if (through_l2) asm volatile("; dW through the L2" ::: "memory");
 #pragma unroll
     for (int i = 0; i < LmCfg::IB; ++i) {
       float old[16][LmCfg::JB];
@@ -724,20 +730,24 @@ __device__ __forceinline__ void lm_dw_tile(const DwArgs& p, int bid, int nblocks
         for (int j = 0; j < LmCfg::JB; ++j) {
           if (!full && n0 + gemm_col<LmCfg>(wn, j, lane) >= p.g.N) continue;
           if (accumulate) o[32 * j] = old[r][j] + acc[i][j][r];
+          else if (through_l2) o[32 * j] = acc[i][j][r];
           else __builtin_nontemporal_store(acc[i][j][r], o + 32 * j);
         }
       }
     }
+    if (through_l2) asm volatile("; dW stored" ::: "memory");
   };
   typedef std::true_type Y;
   typedef std::false_type N;
   const bool full = m0 + TILE <= p.g.M && n0 + TILE <= p.g.N;
   if (full) {
-    if (p.accumulate) store(Y(), Y());
-    else store(Y(), N());
+    if (p.accumulate) store(Y(), Y(), Y());
+    else if (cached) store(Y(), N(), Y());
+    else store(Y(), N(), N());
   } else {
-    if (p.accumulate) store(N(), Y());
-    else store(N(), N());
+    if (p.accumulate) store(N(), Y(), Y());
+    else if (cached) store(N(), N(), Y());
+    else store(N(), N(), N());
   }
 }
 

@@ -88,3 +88,22 @@ def test_forward_only_packed(T, H, V):
 def test_packed_w_where_its_rows_are_not_whole_lines(T, H, V, block, streams):
     # whole dhidden tiles on the packed W from 4,096 rows on where V is not a multiple of 64, a short last block among them
     test_split_dhidden(T, H, V, block, streams)
+
+
+@pytest.mark.parametrize("T,V", [(40, 520), (128, 520), (129, 520), (40, 528)])
+def test_dw_stores_of_few_rows(T, V):
+    # dW written and not added to: through the L2 where its rows are not multiples of 64 bytes and K is at most 128
+    H = 320
+    e = edge_batch(T, H, V, seed=T + V)
+    A32 = oracle.advantages(e["rewards"], e["G"]).astype(np.float32)
+    seg = oracle.segments(T, e["sto"], e["tso"])
+    ref = fused.fused_loss(bits(e["hidden"]), bits(e["W"]), e["actions"], e["behave"], None, A32.astype(np.float64),
+                           seg, e["G"], norm=oracle.NORM_CONST_K, k=4.0, dual_clip_c=3.0)
+    store = torch.full((H * V + 256,), 7.0, device="cuda")
+    grpo.fused_lmhead_grpo_blocked(
+        e["hidden"], e["W"], torch.from_numpy(e["actions"]).cuda(), torch.from_numpy(e["behave"]).cuda(),
+        torch.from_numpy(A32).cuda(), torch.from_numpy(e["sto"]).cuda(), torch.from_numpy(e["tso"]).cuda(), e["G"],
+        norm=gpu_norm(oracle.NORM_CONST_K), k=4.0, dual_clip_c=3.0, dw_lm=store[:H * V].view(H, V))
+    assert (store[H * V:] == 7.0).all()
+    h64 = fused.as_f64(bits(e["hidden"]))
+    check_dw(store[:H * V].view(H, V).cpu().numpy().astype(np.float64), ref.dW, h64, ref.rows.dlogits)

@@ -48,3 +48,14 @@ def test_scanner_finds_the_pattern():
 def test_no_load_reads_a_scalar_too_early(src):
     hits = scan_scalar_reads(_assembly(src))
     assert not hits, "\n".join(f"{fn}: [{a}] then [{b}]" for fn, a, b in hits[:10])
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_backward_products_keep_both_kinds_of_stores():
+    # the compiler takes a non-temporal store and a plain one of the same value for the same and may join them into plain ones
+    src = next(s for s in SOURCES if "lmhead" in str(s))
+    kinds = {}
+    for fn, inst in _instructions(_assembly(src)):
+        if "k_lm_backward" in fn and inst.startswith("global_store_dword "):
+            kinds.setdefault(fn, set()).add(inst.split()[-1] == "nt")
+    assert len(kinds) == 3 and all(k == {True, False} for k in kinds.values()), kinds
