@@ -1241,7 +1241,7 @@ static DhPlan dh_plan(int64_t rows, int64_t H, int64_t V, int accumulate, int64_
   const double slab = V % 64 == 0 ? 1.0 : 1.16, packed_slab = 0.95;
   DhPlan best{1, (int)(nk * 64)};
   double best_t = 0.0;
-  for (int64_t s = 1; s <= 16 && (s == 1 || 4 * s <= nk); ++s) {  // ranges of 4 slabs at least: a tile's first loads take two
+  for (int64_t s = 1; s <= 16 && s <= nk; ++s) {
     const int64_t per = (nk + s - 1) / s, ranges = (nk + per - 1) / per;
     if (ranges < s) continue;
     if (s > 1 && s * rows * H > scratch_floats) break;
